@@ -131,24 +131,58 @@ __device__ __forceinline__ float e4m3_value(uint32_t code) {
   return __builtin_bit_cast(float, b2 << 16);
 }
 
+// The 16 slots of a lane's two dims (2*lane, 2*lane + 1) of one fp8 (page, KV
+// head): dword i holds slots 4q .. 4q + 3 (q = i / 2) of dim 2*lane + i % 2.
+struct E4m3Slots {
+  uint32_t x[8];
+};
+
+__device__ __forceinline__ E4m3Slots load_e4m3_slots(const uint8_t* page, bool is_v, int lane) {
+  E4m3Slots s;
+  if (is_v) {  // two rows of 16 slots
+    typedef u32x4 u32x4_a4 __attribute__((aligned(4)));  // an append's pools are 4-byte aligned
+    const u32x4_a4* rows = reinterpret_cast<const u32x4_a4*>(page) + 2 * lane;
+    const u32x4 r0 = rows[0], r1 = rows[1];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      s.x[2 * q] = r0[q];
+      s.x[2 * q + 1] = r1[q];
+    }
+  } else {  // a dim pair per slot
+    const uint16_t* toks = reinterpret_cast<const uint16_t*>(page) + lane;
+    uint32_t t[kPage];
+#pragma unroll
+    for (int k = 0; k < kPage; ++k) t[k] = toks[k * (kDim / 2)];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      s.x[i] = 0;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) s.x[i] |= ((t[4 * (i >> 1) + b] >> (8 * (i & 1))) & 0xFFu) << (8 * b);
+    }
+  }
+  return s;
+}
+
 // The E4M3 append rule for one token of one (page, KV head) of K (is_v
 // false, page [slot][d]) or V (page [d][slot]), by one wave whose lane holds
-// dims 2 lane, 2 lane + 1; all arithmetic in float32.  The first token of a
-// page sets scale = amax/28 (16x headroom below 448); a later token with
-// amax > 448*scale first re-encodes the page's earlier slots to amax/28; the
-// token is stored as RNE(x/scale).  Returns the page's scale afterwards
-// (old_scale is ignored for slot 0); the caller stores it.
-__device__ float append_e4m3_head(uint8_t* page, float old_scale, int slot, bool is_v,
-                                  const uint16_t* x_bits, int lane) {
+// dims 2 lane, 2 lane + 1 (their bf16 bits in x2); all arithmetic in float32.
+// The first token of a page sets scale = amax/28 (16x headroom below 448); a
+// later token with amax > 448*scale first re-encodes the page's earlier slots
+// to amax/28; the token is stored as RNE(x/scale).  Returns the page's scale
+// afterwards (old_scale is ignored for slot 0); the caller stores it.  The
+// page's slots are loaded when they are re-encoded, all at once, or come with
+// the call (slots, not NULL); V rows are then stored whole.
+__device__ __forceinline__ float append_e4m3_head(uint8_t* page, float old_scale, int slot,
+                                                  bool is_v, uint32_t x2, int lane,
+                                                  const E4m3Slots* slots) {
   const int d0 = 2 * lane;
-  const float x0 = __builtin_bit_cast(float, (uint32_t)x_bits[d0] << 16);
-  const float x1 = __builtin_bit_cast(float, (uint32_t)x_bits[d0 + 1] << 16);
+  const float x0 = __builtin_bit_cast(float, x2 << 16);
+  const float x1 = __builtin_bit_cast(float, x2 & 0xFFFF0000u);
   float amax = fmaxf(fabsf(x0), fabsf(x1));
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) amax = fmaxf(amax, __shfl_xor(amax, m));
-  auto at = [&](int s_, int d_) -> uint8_t* {
-    return page + (is_v ? d_ * kPage + s_ : s_ * kDim + d_);
-  };
+  E4m3Slots old;
+  if (slots) old = *slots;
   float scale;
   if (slot == 0) {
     scale = amax > 0.0f ? amax / 28.0f : 1.0f;
@@ -156,24 +190,91 @@ __device__ float append_e4m3_head(uint8_t* page, float old_scale, int slot, bool
     scale = old_scale;
     if (amax > 448.0f * scale) {
       const float fresh = amax / 28.0f;
-      for (int s_ = 0; s_ < slot; ++s_) {
-        uint8_t* p0 = at(s_, d0);
-        uint8_t* p1 = at(s_, d0 + 1);
-        const float v0 = e4m3_value(*p0) * scale;
-        const float v1 = e4m3_value(*p1) * scale;
-        *p0 = (uint8_t)e4m3_rne(v0 / fresh);
-        *p1 = (uint8_t)e4m3_rne(v1 / fresh);
+      auto redo = [&](uint32_t code) -> uint32_t {
+        return e4m3_rne(e4m3_value(code) * scale / fresh);
+      };
+      if (!slots) old = load_e4m3_slots(page, is_v, lane);
+      uint32_t* rows = reinterpret_cast<uint32_t*>(page) + 4 * d0;
+      uint16_t* toks = reinterpret_cast<uint16_t*>(page) + lane;
+#pragma unroll 1
+      for (int q = 0; q < 4; ++q) {  // x is turned around by a quad of slots each time
+        uint32_t c[2] = {0, 0};
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) {
+            const uint32_t code = (old.x[i] >> (8 * b)) & 0xFFu;
+            c[i] |= (4 * q + b < slot ? redo(code) : code) << (8 * b);
+          }
+        if (is_v) {
+          rows[q] = c[0];
+          rows[4 + q] = c[1];
+        } else {
+#pragma unroll
+          for (int b = 0; b < 4; ++b)
+            if (4 * q + b < slot)
+              toks[(4 * q + b) * (kDim / 2)] =
+                  (uint16_t)(((c[0] >> (8 * b)) & 0xFFu) | ((c[1] >> (8 * b)) & 0xFFu) << 8);
+        }
+#pragma unroll
+        for (int i = 0; i < 6; ++i) old.x[i] = old.x[i + 2];
+        old.x[6] = c[0];
+        old.x[7] = c[1];
       }
       scale = fresh;
     }
   }
-  *at(slot, d0) = (uint8_t)e4m3_rne(x0 / scale);
-  *at(slot, d0 + 1) = (uint8_t)e4m3_rne(x1 / scale);
+  const uint32_t c0 = e4m3_rne(x0 / scale), c1 = e4m3_rne(x1 / scale);
+  if (is_v && slots) {
+    u32x4* rows = reinterpret_cast<u32x4*>(page) + d0;
+    u32x4 r[2];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t keep = slot >> 2 == q ? ~(0xFFu << (8 * (slot & 3))) : ~0u;
+      r[0][q] = (old.x[2 * q] & keep) | (c0 << (8 * (slot & 3)) & ~keep);
+      r[1][q] = (old.x[2 * q + 1] & keep) | (c1 << (8 * (slot & 3)) & ~keep);
+    }
+    rows[0] = r[0];
+    rows[1] = r[1];
+  } else if (is_v) {
+    page[d0 * kPage + slot] = (uint8_t)c0;
+    page[(d0 + 1) * kPage + slot] = (uint8_t)c1;
+  } else {
+    reinterpret_cast<uint16_t*>(page)[slot * (kDim / 2) + lane] = (uint16_t)(c0 | c1 << 8);
+  }
   return scale;
 }
 
+// The token's V elements written into slot `slot` of a bf16 page's 128 rows
+// of 16 slots, by one wave, as whole rows.  A step's appends are bound by what
+// their writes cost the memory afterwards, not by their bytes: 2-byte stores,
+// one per row, leave a partial line in every row, and the attention that
+// follows pays for it (192 sequences of 32 KV heads: partial kernel 235 us
+// after them, 226 us after whole rows; the step 250.3 -> 246.8 us).
+__device__ __forceinline__ void append_v_rows(uint16_t* page, int slot, const uint16_t* v_new,
+                                              int lane) {
+  typedef u32x4 u32x4_a4 __attribute__((aligned(4)));  // an append's pools are 4-byte aligned
+  u32x4_a4* rows = reinterpret_cast<u32x4_a4*>(page);  // two per row
+  u32x4 x[4];
+  uint32_t v[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    x[i] = rows[64 * i + lane];
+    v[i] = v_new[32 * i + (lane >> 1)];
+  }
+  const int wd = (slot & 7) >> 1, sh = 16 * (slot & 1);
+  const bool mine = (lane & 1) == slot >> 3;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (mine && k == wd) x[i][k] = (x[i][k] & ~(0xFFFFu << sh)) | v[i] << sh;
+    rows[64 * i + lane] = x[i];
+  }
+}
+
 template <bool FP8>
-__global__ __launch_bounds__(256) void append_kernel(AppendArgs a) {
+__global__ __launch_bounds__(1024) void append_kernel(AppendArgs a) {
   const int b = blockIdx.x;
   const int r = a.tail_route[b];
   if (r < 0) return;
@@ -203,15 +304,15 @@ __global__ __launch_bounds__(256) void append_kernel(AppendArgs a) {
   const int slot = (te - tb) % kPage;
   const int H = a.num_kv_heads;
   if constexpr (!FP8) {
-    uint16_t* kp = static_cast<uint16_t*>(a.k_pool);
-    uint16_t* vp = static_cast<uint16_t*>(a.v_pool);
-    for (int e = threadIdx.x; e < H * kDim; e += blockDim.x) {
-      const int g = e / kDim, d = e % kDim;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    for (int g = w; g < H; g += nw) {
       const size_t head = pool_slice(pid, g, H, a.num_pages, a.head_major);
-      const uint16_t kv = a.k_new[((size_t)b * H + g) * kDim + d];
-      const uint16_t vv = a.v_new[((size_t)b * H + g) * kDim + d];
-      kp[(head * kPage + slot) * kDim + d] = kv;
-      vp[(head * kDim + d) * kPage + slot] = vv;
+      const size_t tok = ((size_t)b * H + g) * kDim;
+      uint32_t* krow = reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(a.k_pool) +
+                                                   (head * kPage + slot) * kDim);
+      append_v_rows(static_cast<uint16_t*>(a.v_pool) + head * kDim * kPage, slot, a.v_new + tok,
+                    lane);
+      krow[lane] = reinterpret_cast<const uint32_t*>(a.k_new + tok)[lane];
     }
   } else {
     // One wave per (KV head, K|V)
@@ -222,9 +323,9 @@ __global__ __launch_bounds__(256) void append_kernel(AppendArgs a) {
       float* scale = (is_v ? a.v_scale : a.k_scale) + (size_t)pid * H + g;
       uint8_t* page = static_cast<uint8_t*>(is_v ? a.v_pool : a.k_pool) +
                       pool_slice(pid, g, H, a.num_pages, a.head_major) * (kPage * kDim);
-      const float s_new = append_e4m3_head(page, *scale, slot, is_v,
-                                           (is_v ? a.v_new : a.k_new) + ((size_t)b * H + g) * kDim,
-                                           lane);
+      const uint32_t x2 = reinterpret_cast<const uint32_t*>(
+          (is_v ? a.v_new : a.k_new) + ((size_t)b * H + g) * kDim)[lane];
+      const float s_new = append_e4m3_head(page, *scale, slot, is_v, x2, lane, nullptr);
       if (lane == 0) *scale = s_new;
     }
   }
@@ -310,7 +411,9 @@ __device__ __forceinline__ void store_new_token(const PartialArgs& a, const Rout
       // scales are [num_pages][Hkv] in either pool layout
       float* scale = (is_v ? a.v_scale_w : a.k_scale_w) + (size_t)rv.app_pid * H + g;
       uint8_t* page = static_cast<uint8_t*>(is_v ? a.v_pool_w : a.k_pool_w) + head * (kPage * kDim);
-      const float s_new = append_e4m3_head(page, *scale, rv.app_slot, is_v, is_v ? vn : kn, lane);
+      const float s_new = append_e4m3_head(page, *scale, rv.app_slot, is_v,
+                                           reinterpret_cast<const uint32_t*>(is_v ? vn : kn)[lane],
+                                           lane, nullptr);
       if (lane == 0) {
         *scale = s_new;
         s_app[wv] = s_new;
@@ -1085,10 +1188,13 @@ hipError_t scratch_address(void** out) {
 
 hipError_t launch_append(const AppendArgs& a, bool fp8, hipStream_t stream) {
   if (a.num_seqs == 0) return hipSuccess;
+  // a wave per KV head (fp8: and one for K, one for V), at most 16
+  const int waves = fp8 ? 2 * a.num_kv_heads : a.num_kv_heads;
+  const dim3 block(64 * (waves < 16 ? waves : 16));
   if (fp8)
-    hipLaunchKernelGGL(append_kernel<true>, dim3(a.num_seqs), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(append_kernel<true>, dim3(a.num_seqs), block, 0, stream, a);
   else
-    hipLaunchKernelGGL(append_kernel<false>, dim3(a.num_seqs), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(append_kernel<false>, dim3(a.num_seqs), block, 0, stream, a);
   return hipGetLastError();
 }
 
