@@ -200,6 +200,14 @@ int32_t units_per_workgroup(bool fp8, bool route_list, const ChunkPlan& plan, in
              : 1;
 }
 
+// The merge of a fused step also combines a split launch's records unless a
+// sequence may hold so many routes that its one workgroup per head would
+// take them one after another for too long.  Merged: chat batches (8
+// sequences, 9 ranges) 24.2 -> 19.9 us per step, 64 fp8 sequences 62.2 -> 55.4.
+bool merge_combines(int32_t num_routes, int32_t num_seqs) {
+  return num_routes <= 4 * (int64_t)num_seqs + 12;
+}
+
 bool ordered_dispatch(const ChunkPlan& plan, int32_t num_launch, int32_t num_kv_heads,
                       int64_t slots) {
   const int64_t items = (int64_t)plan.max_chunks * num_kv_heads * num_launch;
@@ -507,6 +515,10 @@ int decode_step_impl(const kf_shape* shape, const void* q, void* k_pool, void* v
   ma.page_ids = page_ids;
   ma.num_pages = shape->num_pages;
   ma.num_page_ids = shape->num_page_ids;
+  if (pa.max_chunks > 1 && kf::merge_combines(num_routes, shape->num_seqs)) {
+    pa.merge_combines = 1;
+    ma.rec = kf::records_of(pa);
+  }
   if (kf::launch_partial(pa, fp8, s) != hipSuccess) return KF_ERR_HIP;
   return kf::launch_merge(ma, s) == hipSuccess ? KF_OK : KF_ERR_HIP;
 }

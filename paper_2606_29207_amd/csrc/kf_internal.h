@@ -19,6 +19,10 @@ constexpr int kMinSplitPages = 16;    // smallest page range a split workgroup g
 constexpr int kMinRangePagesMany = 256;  // ... in bf16 launches of at least a round of units
 constexpr int kMaxPagesTwoUnit = 2048;  // longest units run two per workgroup (bf16, unsplit)
 constexpr int kMaxLaunchRoutes = 65535;  // routes per launch and KV heads: grid dimension limits
+constexpr int kChunksOneWave = 8;        // ranges per unit up to which one wave combines a head
+constexpr int kRecordsOneWave = 8;       // mean records per (sequence, head) up to which one wave merges them
+constexpr int kLdsRows = 16;             // rows per sequence that a combining merge keeps in LDS
+constexpr int kMergeRowsFourWaves = 8;   // mean rows per sequence from which four waves merge a head
 constexpr int kOrderBuckets = 64;        // range-size classes of the dispatch order
 constexpr int64_t kMaxOrderItems = int64_t(1) << 20;  // largest split launch given a dispatch order
 
@@ -35,6 +39,17 @@ struct AppendArgs {
   int32_t* err_flags;
   int32_t num_seqs, num_kv_heads, num_routes, num_pages, num_page_ids;
   int32_t head_major;  // pools [Hkv][num_pages][...] instead of [num_pages][Hkv][...]
+};
+
+// The records of a split launch as the combine reads them.
+struct RecordArgs {
+  const float* ml;            // (max, sum) per record; NULL: no records to combine
+  const float* o;             // [kDim] per record
+  float* o_part;
+  float* lse_part;
+  const int32_t* route_list;  // as in PartialArgs
+  int32_t num_routes, num_q_heads, num_kv_heads, group;
+  int32_t max_chunks;
 };
 
 struct PartialArgs {
@@ -55,6 +70,7 @@ struct PartialArgs {
   int32_t num_routes, max_pages_per_route;
   int32_t num_units_routes;  // routes launched: num_list, or num_routes without a list
   int32_t chunk_pages, max_chunks;  // a unit of n pages uses ceil(n / chunk_pages) workgroups
+  int32_t merge_combines;  // the merge kernel of a fused step combines the records
   int32_t units_per_wg;  // 2: unsplit bf16 launch, two units per 512-thread workgroup
   // Split launches of several rounds: the dispatch order of the work items,
   // written by order_kernel before the partial kernel runs (NULL: grid
@@ -91,7 +107,13 @@ struct MergeArgs {
   const int32_t* tail_route;
   const int32_t* page_ids;
   int32_t num_pages, num_page_ids;
+  RecordArgs rec;  // rec.ml set: combine these records before merging
 };
+
+inline RecordArgs records_of(const PartialArgs& a) {
+  return {a.ws_ml, a.ws_o, a.o_part, a.lse_part, a.route_list, a.num_routes, a.num_q_heads,
+          a.num_kv_heads, a.group, a.max_chunks};
+}
 
 struct WorkspaceLayout {
   size_t ml_off, o_off, order_off, total;  // order_off: 0 without a dispatch order
@@ -126,6 +148,9 @@ ChunkPlan plan_chunks(int32_t num_routes, int32_t num_kv_heads, int32_t max_page
 // (1 or 2); route_list: a launch over a route list (kf_partial_attn_subset).
 int32_t units_per_workgroup(bool fp8, bool route_list, const ChunkPlan& plan, int32_t num_launch,
                             int32_t num_kv_heads, int32_t max_pages_per_route);
+// Whether the merge kernel of a fused step also combines the records of a
+// split launch.
+bool merge_combines(int32_t num_routes, int32_t num_seqs);
 // A split launch of at least two rounds of the GPU's `slots` resident
 // workgroups (and at most kMaxOrderItems work items) runs its work items
 // in a computed order, largest ranges first (order_kernel).

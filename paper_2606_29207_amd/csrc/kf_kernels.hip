@@ -72,6 +72,11 @@ __device__ __forceinline__ f32x4 mfma16(u32x4 a, u32x4 b, f32x4 c) {
 
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// Lane i's value of x, i uniform over the wave.
+__device__ __forceinline__ float read_lane(float x, int i) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), i));
+}
+
 __device__ __forceinline__ uint32_t pack_bf16_rne(float lo, float hi) {
   bf16x2 v = {(__bf16)lo, (__bf16)hi};
   return __builtin_bit_cast(uint32_t, v);
@@ -464,6 +469,118 @@ struct TileRaw<true> {
   float ks, vs;   // K and V scales of the lane's page (vpage)
 };
 
+// Softmax state of one query head per lane column: lane (grp, li) holds dims
+// 16*b8 + 4*grp + r4 of head li; m is shared by the four lane groups, l is
+// the lane's own part of the sum.
+struct Attn {
+  f32x4 o[8];
+  float m, l;
+};
+
+__device__ __forceinline__ void reset(Attn& s) {
+#pragma unroll
+  for (int b8 = 0; b8 < 8; ++b8) s.o[b8] = f32x4{0.f, 0.f, 0.f, 0.f};
+  s.m = neg_inf();
+  s.l = 0.0f;
+}
+
+// One tile: scores, softmax update, O^T += V^T P^T.  ks: score scale (with
+// the page's K scale), vs: V scale, of the lane's page; tok0: the lane's
+// first route-local token, lim: the token bound.  MASK: the tile can hold
+// slots past the bound; their V bits are zeroed and they add nothing.
+template <bool FP8, bool MASK>
+__device__ __forceinline__ void attend(const TileRaw<FP8>& t, const u32x4 (&qb)[4], float ks,
+                                       float vs, int tok0, int lim, Attn& st) {
+  constexpr int NC = Geo<FP8>::NC, NH = Geo<FP8>::NH;
+  // ---- S^T = K Q^T (fp8 codes widen to bf16 right before their MFMA)
+  f32x4 s[NC];
+#pragma unroll
+  for (int cc = 0; cc < NC; ++cc) {
+    s[cc] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (!FP8) {
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) s[cc] = mfma16(t.k[cc][kk], qb[kk], s[cc]);
+    } else {
+#pragma unroll
+      for (int pp = 0; pp < 2; ++pp) {
+        u32x4 k0, k1;
+        fp8x16_to_bf16(t.k[cc][pp], k0, k1);
+        s[cc] = mfma16(k0, qb[2 * pp], s[cc]);
+        s[cc] = mfma16(k1, qb[2 * pp + 1], s[cc]);
+      }
+    }
+  }
+  float mt = neg_inf();
+#pragma unroll
+  for (int cc = 0; cc < NC; ++cc)
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const float v = (tok0 + 4 * cc + r4 < lim) ? s[cc][r4] * ks : neg_inf();
+      s[cc][r4] = v;
+      mt = fmaxf(mt, v);
+    }
+  mt = fmaxf(mt, __shfl_xor(mt, 16));
+  mt = fmaxf(mt, __shfl_xor(mt, 32));
+  const float m_new = fmaxf(st.m, mt);
+  const float alpha = exp2_fast(st.m - m_new);
+  st.m = m_new;
+  st.l *= alpha;
+#pragma unroll
+  for (int b8 = 0; b8 < 8; ++b8) st.o[b8] *= alpha;
+
+  // ---- P^T operands: half h2 holds slots 8*h2 + j (j < 8) of the lane's
+  // range, i.e. MFMA c = 2*h2 + j/4, row r4 = j%4; bf16 hi + lo
+  u32x4 phi[NH], plo[NH];
+#pragma unroll
+  for (int h2 = 0; h2 < NH; ++h2)
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      const int cc = 2 * h2 + (jj >> 1), r4 = 2 * (jj & 1);
+      const float e0 = exp2_fast(s[cc][r4] - m_new);
+      const float e1 = exp2_fast(s[cc][r4 + 1] - m_new);
+      st.l += e0 + e1;
+      float x0 = e0 * vs, x1 = e1 * vs;
+      if constexpr (MASK && FP8) {  // a masked slot adds nothing, whatever its page's scales
+        const int t0 = tok0 + 8 * h2 + 2 * jj;
+        x0 = t0 < lim ? x0 : 0.0f;
+        x1 = t0 + 1 < lim ? x1 : 0.0f;
+      }
+      const uint32_t b0 = __builtin_bit_cast(uint32_t, x0) & 0xFFFF0000u;
+      const uint32_t b1 = __builtin_bit_cast(uint32_t, x1) & 0xFFFF0000u;
+      phi[h2][jj] = (b0 >> 16) | b1;
+      plo[h2][jj] = pack_bf16_rne(x0 - __builtin_bit_cast(float, b0),
+                                  x1 - __builtin_bit_cast(float, b1));
+    }
+
+  // ---- O^T += V^T P^T; V of slots past the range is zeroed (unused slots
+  // may hold anything)
+  uint32_t msk[NH][4];
+#pragma unroll
+  for (int h2 = 0; h2 < NH; ++h2)
+#pragma unroll
+    for (int wd = 0; wd < 4; ++wd) {
+      const int t0 = tok0 + 8 * h2 + 2 * wd;
+      msk[h2][wd] = (t0 < lim ? 0x0000FFFFu : 0u) | (t0 + 1 < lim ? 0xFFFF0000u : 0u);
+    }
+#pragma unroll
+  for (int b8 = 0; b8 < 8; ++b8) {
+    u32x4 vr[NH];
+    if constexpr (!FP8) vr[0] = t.v[b8];
+    else fp8x16_to_bf16(t.v[b8], vr[0], vr[1]);
+    if constexpr (MASK) {
+#pragma unroll
+      for (int h2 = 0; h2 < NH; ++h2)
+#pragma unroll
+        for (int wd = 0; wd < 4; ++wd) vr[h2][wd] &= msk[h2][wd];
+    }
+#pragma unroll
+    for (int h2 = 0; h2 < NH; ++h2) {
+      st.o[b8] = mfma16(vr[h2], phi[h2], st.o[b8]);
+      st.o[b8] = mfma16(vr[h2], plo[h2], st.o[b8]);
+    }
+  }
+}
+
 // Wave-uniform description of one tile: its first route-local page and the
 // page ids of its (up to four) pages.
 struct TileInfo {
@@ -476,6 +593,18 @@ __device__ __forceinline__ T pick4(T v0, T v1, T v2, T v3, int i) {
   return (i & 2) ? ((i & 1) ? v3 : v2) : ((i & 1) ? v1 : v0);
 }
 
+// Record marks of a split launch, so that the combine needs no route row: a
+// unit whose outputs are already in o_part/lse_part carries the sum -1 in its
+// first record (a real sum is >= 0 or NaN), an unused record place the
+// maximum -inf and the sum 0.
+__device__ __forceinline__ void mark_whole(const PartialArgs& a, int u, int g, int tid) {
+  const size_t rec = ((size_t)u * a.num_kv_heads + g) * a.max_chunks;
+  if (tid < a.group) {
+    a.ws_ml[(rec * a.group + tid) * 2] = 0.0f;
+    a.ws_ml[(rec * a.group + tid) * 2 + 1] = -1.0f;
+  }
+}
+
 // UPW = units per workgroup.  1: a 256-thread workgroup owns one (route, KV
 // head) unit or one chunk of it, two workgroups per CU.  2 (unsplit bf16
 // launches of units of at most kMaxPagesTwoUnit pages): a 512-thread
@@ -486,7 +615,7 @@ __device__ __forceinline__ T pick4(T v0, T v1, T v2, T v3, int i) {
 template <bool FP8, int UPW, bool HM>
 __global__ __launch_bounds__(kThreads * UPW, 2 / UPW) void partial_kernel(PartialArgs a) {
   using GeoT = Geo<FP8>;
-  constexpr int TP = GeoT::TP, NC = GeoT::NC, NH = GeoT::NH;
+  constexpr int TP = GeoT::TP, NC = GeoT::NC;
   __shared__ float s_o_u[UPW][kWaves][KF_MAX_GROUP][kLdsStride];
   __shared__ float s_m_u[UPW][kWaves][KF_MAX_GROUP];
   __shared__ float s_l_u[UPW][kWaves][KF_MAX_GROUP];
@@ -554,6 +683,7 @@ __global__ __launch_bounds__(kThreads * UPW, 2 / UPW) void partial_kernel(Partia
             a.o_part[((size_t)r * Hq + hq0 + e / kDim) * kDim + e % kDim] = ov;
           if (tid < G) a.lse_part[(size_t)r * Hq + hq0 + tid] = lv;
           if (rv.bad && tid == 0) atomicOr(a.err_flags, KF_EFLAG_BAD_ROUTE);
+          if (UPW == 1 && a.max_chunks > 1) mark_whole(a, u, g, tid);
         }
       } else {
         nchunks = (rv.npages + a.chunk_pages - 1) / a.chunk_pages;
@@ -668,34 +798,13 @@ __global__ __launch_bounds__(kThreads * UPW, 2 / UPW) void partial_kernel(Partia
                            : u32x4{0, 0, 0, 0};
   }
 
-  f32x4 oacc[8];
-#pragma unroll
-  for (int b8 = 0; b8 < 8; ++b8) oacc[b8] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_run = neg_inf(), l_run = 0.0f;
+  Attn acc;
+  reset(acc);
 
-  // MASK: V bits of slots past the range are zeroed (all ones for a full
-  // tile).  Only a wave's final tile can hold such slots, so masking is a
-  // compile-time property and the steady-state loop has no branch.
+  // MASK: only a wave's final tile can hold slots past the range, so masking
+  // is a compile-time property and the steady-state loop has no branch.
   auto compute = [&](const TileRaw<FP8>& t, const TileInfo& ti, auto mask_tag) {
     constexpr bool MASK = decltype(mask_tag)::value;
-    // ---- S^T = K Q^T (fp8 codes widen to bf16 right before their MFMA)
-    f32x4 s[NC];
-#pragma unroll
-    for (int cc = 0; cc < NC; ++cc) {
-      s[cc] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if constexpr (!FP8) {
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) s[cc] = mfma16(t.k[cc][kk], qb[kk], s[cc]);
-      } else {
-#pragma unroll
-        for (int pp = 0; pp < 2; ++pp) {
-          u32x4 k0, k1;
-          fp8x16_to_bf16(t.k[cc][pp], k0, k1);
-          s[cc] = mfma16(k0, qb[2 * pp], s[cc]);
-          s[cc] = mfma16(k1, qb[2 * pp + 1], s[cc]);
-        }
-      }
-    }
     float ks = a.scale_log2, vs = 1.0f;
     if constexpr (FP8) {
       float kss = t.ks;
@@ -707,75 +816,7 @@ __global__ __launch_bounds__(kThreads * UPW, 2 / UPW) void partial_kernel(Partia
       ks *= kss;
     }
     const int tok0 = (ti.tp0 + vpage) * kPage + GeoT::vslot0(grp);  // route-local token, c = r4 = 0
-    float mt = neg_inf();
-#pragma unroll
-    for (int cc = 0; cc < NC; ++cc)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        const float v = (tok0 + 4 * cc + r4 < lim) ? s[cc][r4] * ks : neg_inf();
-        s[cc][r4] = v;
-        mt = fmaxf(mt, v);
-      }
-    mt = fmaxf(mt, __shfl_xor(mt, 16));
-    mt = fmaxf(mt, __shfl_xor(mt, 32));
-    const float m_new = fmaxf(m_run, mt);
-    const float alpha = exp2_fast(m_run - m_new);
-    m_run = m_new;
-    l_run *= alpha;
-#pragma unroll
-    for (int b8 = 0; b8 < 8; ++b8) oacc[b8] *= alpha;
-
-    // ---- P^T operands: half h2 holds slots 8*h2 + j (j < 8) of the lane's
-    // range, i.e. MFMA c = 2*h2 + j/4, row r4 = j%4; bf16 hi + lo
-    u32x4 phi[NH], plo[NH];
-#pragma unroll
-    for (int h2 = 0; h2 < NH; ++h2)
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        const int cc = 2 * h2 + (jj >> 1), r4 = 2 * (jj & 1);
-        const float e0 = exp2_fast(s[cc][r4] - m_new);
-        const float e1 = exp2_fast(s[cc][r4 + 1] - m_new);
-        l_run += e0 + e1;
-        float x0 = e0 * vs, x1 = e1 * vs;
-        if constexpr (MASK && FP8) {  // a masked slot adds nothing, whatever its page's scales
-          const int t0 = tok0 + 8 * h2 + 2 * jj;
-          x0 = t0 < lim ? x0 : 0.0f;
-          x1 = t0 + 1 < lim ? x1 : 0.0f;
-        }
-        const uint32_t b0 = __builtin_bit_cast(uint32_t, x0) & 0xFFFF0000u;
-        const uint32_t b1 = __builtin_bit_cast(uint32_t, x1) & 0xFFFF0000u;
-        phi[h2][jj] = (b0 >> 16) | b1;
-        plo[h2][jj] = pack_bf16_rne(x0 - __builtin_bit_cast(float, b0),
-                                    x1 - __builtin_bit_cast(float, b1));
-      }
-
-    // ---- O^T += V^T P^T; V of slots past the range is zeroed (unused slots
-    // may hold anything)
-    uint32_t msk[NH][4];
-#pragma unroll
-    for (int h2 = 0; h2 < NH; ++h2)
-#pragma unroll
-      for (int wd = 0; wd < 4; ++wd) {
-        const int t0 = tok0 + 8 * h2 + 2 * wd;
-        msk[h2][wd] = (t0 < lim ? 0x0000FFFFu : 0u) | (t0 + 1 < lim ? 0xFFFF0000u : 0u);
-      }
-#pragma unroll
-    for (int b8 = 0; b8 < 8; ++b8) {
-      u32x4 vr[NH];
-      if constexpr (!FP8) vr[0] = t.v[b8];
-      else fp8x16_to_bf16(t.v[b8], vr[0], vr[1]);
-      if constexpr (MASK) {
-#pragma unroll
-        for (int h2 = 0; h2 < NH; ++h2)
-#pragma unroll
-          for (int wd = 0; wd < 4; ++wd) vr[h2][wd] &= msk[h2][wd];
-      }
-#pragma unroll
-      for (int h2 = 0; h2 < NH; ++h2) {
-        oacc[b8] = mfma16(vr[h2], phi[h2], oacc[b8]);
-        oacc[b8] = mfma16(vr[h2], plo[h2], oacc[b8]);
-      }
-    }
+    attend<FP8, MASK>(t, qb, ks, vs, tok0, lim, acc);
   };
 
   // ---- two register buffers: while one tile is computed, the loads of the
@@ -818,6 +859,7 @@ __global__ __launch_bounds__(kThreads * UPW, 2 / UPW) void partial_kernel(Partia
     else compute(ra, ia, masked);
   }
 
+  float m_run = acc.m, l_run = acc.l;
   l_run += __shfl_xor(l_run, 16);
   l_run += __shfl_xor(l_run, 32);
   const bool wave_bad = __ballot(pid_bad) != 0;
@@ -827,7 +869,7 @@ __global__ __launch_bounds__(kThreads * UPW, 2 / UPW) void partial_kernel(Partia
   if (li < G) {
 #pragma unroll
     for (int b8 = 0; b8 < 8; ++b8)
-      *reinterpret_cast<f32x4*>(&s_o[w][li][16 * b8 + 4 * grp]) = oacc[b8];
+      *reinterpret_cast<f32x4*>(&s_o[w][li][16 * b8 + 4 * grp]) = acc.o[b8];
     if (grp == 0) {
       s_m[w][li] = m_run;
       s_l[w][li] = l_run;
@@ -870,16 +912,23 @@ __global__ __launch_bounds__(kThreads * UPW, 2 / UPW) void partial_kernel(Partia
     }
     if (tid < G)
       a.lse_part[(size_t)r * Hq + hq0 + tid] = (s_fm[tid] + __log2f(s_fl[tid])) * kLn2;
+    if (UPW == 1 && a.max_chunks > 1) mark_whole(a, u, g, tid);
     return;
   }
-  // chunked unit: unnormalised output and (max, sum) of this page range
+  // chunked unit: unnormalised output and (max, sum) of this page range; the
+  // unit's last range marks the record places that the unit leaves unused
   const size_t rec = ((size_t)u * H + g) * a.max_chunks + c;
+  if (c == nchunks - 1)
+    for (int e = tid; e < (a.max_chunks - nchunks) * G; e += kThreads) {
+      a.ws_ml[((rec + 1) * G + e) * 2] = neg_inf();
+      a.ws_ml[((rec + 1) * G + e) * 2 + 1] = 0.0f;
+    }
   for (int e = tid; e < G * kDim; e += kThreads) {
     const int h = e / kDim, d = e % kDim;
     float O = 0.0f;
 #pragma unroll
     for (int ww = 0; ww < kWaves; ++ww) O += s_m[ww][h] * s_o[ww][h][d];
-    a.ws_o[(rec * G + h) * kDim + d] = O;
+    __builtin_nontemporal_store(O, &a.ws_o[(rec * G + h) * kDim + d]);
   }
   if (tid < G) {
     a.ws_ml[(rec * G + tid) * 2] = s_fm[tid];
@@ -962,54 +1011,140 @@ __global__ __launch_bounds__(1024) void order_kernel(PartialArgs a) {
   }
 }
 
-// Combine the chunk partials of each chunked (route, KV head) in chunk order.
-// Wave w reduces heads w, w+4, ...: its lanes read up to 64 chunks' (max,
-// sum) at once; then every thread sums its output elements over the chunks
-// in chunk order, four chunks' loads in flight at a time.
-__global__ __launch_bounds__(kThreads) void combine_kernel(PartialArgs a) {
-  __shared__ float s_fm[KF_MAX_GROUP];
-  __shared__ float s_fl[KF_MAX_GROUP];
-  const int g = blockIdx.x, u = blockIdx.y, tid = threadIdx.x;
-  const int lane = tid & 63, w = tid >> 6;
-  const int G = a.group, Hq = a.num_q_heads, H = a.num_kv_heads;
+// The records of one (launch position, query head): k places, `stride`
+// records apart; those in use come first.
+struct Pieces {
+  size_t rec0;
+  int stride, k;
+};
+
+__device__ __forceinline__ Pieces pieces_of(const RecordArgs& a, int u, int h) {
+  const int g = h / a.group, hl = h - g * a.group;
+  return {(((size_t)u * a.num_kv_heads + g) * a.max_chunks) * a.group + hl, a.group, a.max_chunks};
+}
+
+// Weighted output sums of up to 64 records (record base + i: weight wi in lane
+// off + i, bit i of `used` set if it holds anything), dims 2*lane and 2*lane + 1, added to four subsets of
+// records (subset s: s, s + 4, ...), each in record order.  WAVES = 4: this
+// wave's subset only; WAVES = 1: all four.  Eight records' loads in flight.
+template <int WAVES>
+__device__ __forceinline__ void piece_sums(const RecordArgs& a, const Pieces& p, int base,
+                                           uint64_t used, float wi, int off, int lane, int wave,
+                                           float2 (&acc)[4 / WAVES]) {
+  constexpr int NS = 4 / WAVES, UN = 8 / NS;
+  // places not in use (and ranges whose every score is -inf) add nothing
+  const int cnt = used ? 64 - __builtin_clzll(used) : 0;
+  const float2* o = reinterpret_cast<const float2*>(a.o) + lane;
+  for (int j = WAVES == 1 ? 0 : wave; j < cnt; j += 4 * UN) {
+    float2 v[UN][NS];
+    float wt[UN][NS];
+#pragma unroll
+    for (int q = 0; q < UN; ++q)
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const int jj = min(j + 4 * q + s, cnt - 1);
+        const bool in = j + 4 * q + s < cnt && ((used >> jj) & 1);
+        const float w = read_lane(wi, off + jj);
+        wt[q][s] = in ? w : 0.0f;
+        v[q][s] = o[(p.rec0 + (size_t)(base + jj) * p.stride) * (kDim / 2)];
+        if (!in) v[q][s] = make_float2(0.0f, 0.0f);
+      }
+#pragma unroll
+    for (int q = 0; q < UN; ++q)
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        acc[s].x += wt[q][s] * v[q][s].x;
+        acc[s].y += wt[q][s] * v[q][s].y;
+      }
+  }
+}
+
+// Reduce the records of one (launch position, query head) to the normalised
+// output (the lane's dims) and lse; false: the outputs are already in place.
+// WAVES = 4: called by the 256 threads of a workgroup, and the result is wave
+// 0's; WAVES = 1: by one wave.  The same bits either way: every wave forms
+// the maximum and the sum alike, the outputs add up as ((S0 + S1) + S2) + S3.
+template <int WAVES>
+__device__ __forceinline__ bool combine_unit(const RecordArgs& a, const Pieces& p, int lane,
+                                             int wave, float2 (*s_sum)[64], float2& o, float& lse) {
+  const float2* ml = reinterpret_cast<const float2*>(a.ml) + p.rec0;
+  auto record = [&](int i) -> float2 {
+    return i < p.k ? ml[(size_t)i * p.stride] : make_float2(neg_inf(), 0.0f);
+  };
+  const float2 first = record(lane);  // all of them, with up to 64 places
+  if (__shfl(first.y, 0) == -1.0f) return false;
+  float M = first.x;
+  for (int i = lane + 64; i < p.k; i += 64) M = fmaxf(M, record(i).x);
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) M = fmaxf(M, __shfl_xor(M, m));
+  auto weight = [&](float m) { return m == neg_inf() ? 0.0f : exp2_fast(m - M); };
+  float w = weight(first.x), L = first.x == neg_inf() ? 0.0f : w * first.y;
+  float2 acc[4 / WAVES];
+#pragma unroll
+  for (int s = 0; s < 4 / WAVES; ++s) acc[s] = make_float2(0.0f, 0.0f);
+  piece_sums<WAVES>(a, p, 0, __ballot(first.x != neg_inf()), w, 0, lane, wave, acc);
+  for (int base = 64; base < p.k; base += 64) {
+    const float2 r = record(base + lane);
+    w = weight(r.x);
+    L += r.x == neg_inf() ? 0.0f : w * r.y;
+    piece_sums<WAVES>(a, p, base, __ballot(r.x != neg_inf()), w, 0, lane, wave, acc);
+  }
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) L += __shfl_xor(L, m);
+  float2 t;
+  if constexpr (WAVES == 4) {
+    s_sum[wave][lane] = acc[0];
+    __syncthreads();
+    t = s_sum[0][lane];
+#pragma unroll
+    for (int s = 1; s < 4; ++s) {
+      t.x += s_sum[s][lane].x;
+      t.y += s_sum[s][lane].y;
+    }
+    __syncthreads();  // s_sum may be used again
+  } else {
+    t = acc[0];
+#pragma unroll
+    for (int s = 1; s < 4; ++s) {
+      t.x += acc[s].x;
+      t.y += acc[s].y;
+    }
+  }
+  o = make_float2(t.x / L, t.y / L);
+  lse = (M + __log2f(L)) * kLn2;
+  return true;
+}
+
+__device__ __forceinline__ void store_row(const RecordArgs& a, int r, int h, int lane, float2 o,
+                                          float lse) {
+  const size_t row = (size_t)r * a.num_q_heads + h;
+  reinterpret_cast<float2*>(a.o_part)[row * (kDim / 2) + lane] = o;
+  if (lane == 0) a.lse_part[row] = lse;
+}
+
+// Small and bound by its chain of dependent loads, so the chain is short:
+// every (max, sum) of a head arrives in one load and its weights are read
+// across lanes, no route row is read (mark_whole), eight records' outputs are
+// in flight, and the records themselves are written past the L2
+// (non-temporal), where the next kernel finds them on every XCD.  Of 164 units
+// with 16 heads and 13 ranges: 18.3 -> 10 us.
+//
+// Combine the records of each (launch position, query head) whose outputs are
+// not in place yet: one wave each (four heads per workgroup), or, with many
+// records, the four waves of a workgroup.
+template <int WAVES>
+__global__ __launch_bounds__(kThreads) void combine_kernel(RecordArgs a) {
+  __shared__ float2 s_sum[4][64];
+  const int u = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int h = WAVES == 4 ? blockIdx.x : blockIdx.x * 4 + wave;
+  if (h >= a.num_q_heads) return;
   const int r = a.route_list ? a.route_list[u] : u;
   if (r < 0 || r >= a.num_routes) return;  // flagged by partial_kernel
-  const RouteView rv = read_route(a, r);
-  if (rv.bad || rv.npages == 0) return;  // written by partial_kernel
-  const int nchunks = (rv.npages + a.chunk_pages - 1) / a.chunk_pages;
-  if (nchunks == 1) return;              // written by partial_kernel
-  const size_t rec0 = ((size_t)u * H + g) * a.max_chunks;
-  for (int h = w; h < G; h += kWaves) {
-    float M = neg_inf();
-    for (int c = lane; c < nchunks; c += 64) M = fmaxf(M, a.ws_ml[((rec0 + c) * G + h) * 2]);
-    for (int m = 32; m >= 1; m >>= 1) M = fmaxf(M, __shfl_xor(M, m));
-    float L = 0.0f;
-    for (int c = lane; c < nchunks; c += 64) {
-      const float mc = a.ws_ml[((rec0 + c) * G + h) * 2];
-      const float lc = a.ws_ml[((rec0 + c) * G + h) * 2 + 1];
-      L += mc == neg_inf() ? 0.0f : exp2_fast(mc - M) * lc;
-    }
-    for (int m = 32; m >= 1; m >>= 1) L += __shfl_xor(L, m);
-    if (lane == 0) {
-      s_fm[h] = M;
-      s_fl[h] = L;
-    }
-  }
-  __syncthreads();
-  const int hq0 = g * G;
-  for (int e = tid; e < G * kDim; e += kThreads) {
-    const int h = e / kDim, d = e % kDim;
-    const float M = s_fm[h];
-    float O = 0.0f;
-#pragma unroll 4
-    for (int c = 0; c < nchunks; ++c) {
-      const float mc = a.ws_ml[((rec0 + c) * G + h) * 2];
-      const float oc = a.ws_o[((rec0 + c) * G + h) * kDim + d];
-      O += mc == neg_inf() ? 0.0f : exp2_fast(mc - M) * oc;
-    }
-    a.o_part[((size_t)r * Hq + hq0 + h) * kDim + d] = O / s_fl[h];
-  }
-  if (tid < G) a.lse_part[(size_t)r * Hq + hq0 + tid] = (s_fm[tid] + __log2f(s_fl[tid])) * kLn2;
+  float2 o;
+  float lse;
+  if (combine_unit<WAVES>(a, pieces_of(a, u, h), lane, wave, s_sum, o, lse) &&
+      (WAVES == 1 || wave == 0))
+    store_row(a, r, h, lane, o, lse);
 }
 
 // ------------------------------------------------------------------- gather
@@ -1062,12 +1197,164 @@ __device__ __forceinline__ int tail_append_status(const MergeArgs& a, int b, int
   return 1;
 }
 
-// One wave per (query head, sequence); lane holds dims 2*lane, 2*lane+1.
-// In a fused step, wave (0, b) also advances sequence b's tail.
-__global__ __launch_bounds__(64) void merge_kernel(MergeArgs a) {
-  const int h = blockIdx.x, b = blockIdx.y, lane = threadIdx.x;
+// Bound by reading the rows once more rows arrive than one wave's loads in
+// flight cover: 128 rows per sequence (32 sequences, 32 heads, 68 MB) took
+// 16.1 us with one wave of four loads, 12.5 us with four waves of eight (16
+// each: 13.2); below eight rows a sequence one wave is enough.
+//
+// Sequence b's rows r0 .. r0 + n - 1 of query head h merged by WAVES waves;
+// lane holds dims 2*lane, 2*lane+1.  Rows are summed in four subsets (subset
+// s: rows s, s + 4, ...), each in row order, then ((S0 + S1) + S2) + S3: the
+// same bits for one wave and for four.
+template <int WAVES>
+__device__ __forceinline__ void merge_rows(const MergeArgs& a, int b, int h, int r0, int n, int lane,
+                                           int wave, float3 (*s_sum)[64], float* s_max) {
+  constexpr float kLog2e = 1.44269504088896340736f;
+  constexpr int NS = 4 / WAVES, UN = 8 / NS;  // eight rows' loads in flight
   const int Hq = a.num_q_heads;
-  if (a.tail_route && h == 0 && lane == 0) {
+  const float* lse = a.lse_part + (size_t)r0 * Hq + h;
+  float2* out = reinterpret_cast<float2*>(a.out + ((size_t)b * Hq + h) * kDim) + lane;
+  float* lse_out = a.lse_out + (size_t)b * Hq + h;
+  float M = neg_inf();
+  bool nan_seen = false;
+  for (int i = WAVES == 1 ? lane : 64 * wave + lane; i < n; i += 64 * WAVES) {
+    const float l = lse[(size_t)i * Hq];
+    nan_seen |= l != l;
+    M = fmaxf(M, l);
+  }
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) M = fmaxf(M, __shfl_xor(M, m));
+  if (__ballot(nan_seen) != 0) M = qnan();
+  if constexpr (WAVES == 4) {
+    if (lane == 0) s_max[wave] = M;
+    __syncthreads();
+    M = neg_inf();
+    bool any = false;
+    for (int w = 0; w < 4; ++w) {
+      any |= s_max[w] != s_max[w];
+      M = fmaxf(M, s_max[w]);
+    }
+    if (any) M = qnan();
+  }
+  if (M != M || M == neg_inf()) {  // a NaN row; no rows or only empty ones
+    if (WAVES == 1 || wave == 0) {
+      const float v = M != M ? qnan() : 0.0f;
+      *out = make_float2(v, v);
+      if (lane == 0) *lse_out = M;
+    }
+    return;
+  }
+  float3 acc[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) acc[s] = make_float3(0.0f, 0.0f, 0.0f);
+  const size_t rs = (size_t)Hq * kDim / 2;  // float2 elements from one row to the next
+  const float2* o = reinterpret_cast<const float2*>(a.o_part + ((size_t)r0 * Hq + h) * kDim) + lane;
+  constexpr int BLOCK = 64 * WAVES;  // rows whose weights one block of lanes holds
+  for (int base = 0; base < n; base += BLOCK) {
+    // one wave: row base + lane; four: row base + 4 * lane + wave
+    const int i = WAVES == 1 ? base + lane : base + 4 * lane + wave;
+    const float wl = i < n ? exp2_fast((lse[(size_t)i * Hq] - M) * kLog2e) : 0.0f;
+    const int cnt = min(BLOCK, n - base);
+    for (int j = WAVES == 1 ? 0 : wave; j < cnt; j += 4 * UN) {
+      float2 v[UN][NS];
+      float wr[UN][NS];
+#pragma unroll
+      for (int q = 0; q < UN; ++q)
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          const int jj = j + 4 * q + s;
+          const int jc = min(jj, cnt - 1);
+          const float wj = read_lane(wl, WAVES == 1 ? jc : jc >> 2);
+          wr[q][s] = jj < cnt ? wj : 0.0f;
+          v[q][s] = o[(size_t)(base + jc) * rs];
+          if (jj >= cnt) v[q][s] = make_float2(0.0f, 0.0f);
+        }
+#pragma unroll
+      for (int q = 0; q < UN; ++q)
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          acc[s].x += wr[q][s] * v[q][s].x;
+          acc[s].y += wr[q][s] * v[q][s].y;
+          acc[s].z += wr[q][s];
+        }
+    }
+  }
+  float3 t;
+  if constexpr (WAVES == 4) {
+    s_sum[wave][lane] = acc[0];
+    __syncthreads();
+    if (wave != 0) return;
+    t = s_sum[0][lane];
+#pragma unroll
+    for (int s = 1; s < 4; ++s) {
+      t.x += s_sum[s][lane].x;
+      t.y += s_sum[s][lane].y;
+      t.z += s_sum[s][lane].z;
+    }
+  } else {
+    t = acc[0];
+#pragma unroll
+    for (int s = 1; s < 4; ++s) {
+      t.x += acc[s].x;
+      t.y += acc[s].y;
+      t.z += acc[s].z;
+    }
+  }
+  *out = make_float2(t.x / t.z, t.y / t.z);
+  if (lane == 0) *lse_out = M + __logf(t.z);
+}
+
+// merge_rows<1> over rows held in LDS (n <= kLdsRows), by one wave; the same
+// order of sums, so the same bits.
+__device__ __forceinline__ void merge_lds_rows(const MergeArgs& a, int b, int h, int n, int lane,
+                                               const float2 (*s_row)[64], const float* s_lse) {
+  constexpr float kLog2e = 1.44269504088896340736f;
+  const size_t at = (size_t)b * a.num_q_heads + h;
+  float2* out = reinterpret_cast<float2*>(a.out + at * kDim) + lane;
+  const float l = lane < n ? s_lse[lane] : neg_inf();
+  float M = l;
+#pragma unroll
+  for (int m = kLdsRows / 2; m >= 1; m >>= 1) M = fmaxf(M, __shfl_xor(M, m));
+  M = read_lane(M, 0);
+  const bool nan = __ballot(l != l) != 0;
+  if (nan || M == neg_inf()) {
+    const float v = nan ? qnan() : 0.0f;
+    *out = make_float2(v, v);
+    if (lane == 0) a.lse_out[at] = nan ? qnan() : neg_inf();
+    return;
+  }
+  const float wl = lane < n ? exp2_fast((l - M) * kLog2e) : 0.0f;
+  float3 acc[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) acc[s] = make_float3(0.0f, 0.0f, 0.0f);
+  for (int j = 0; j < n; j += 4)
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      if (j + s < n) {
+        const float w = read_lane(wl, j + s);
+        const float2 v = s_row[j + s][lane];
+        acc[s].x += w * v.x;
+        acc[s].y += w * v.y;
+        acc[s].z += w;
+      }
+  float3 t = acc[0];
+#pragma unroll
+  for (int s = 1; s < 4; ++s) {
+    t.x += acc[s].x;
+    t.y += acc[s].y;
+    t.z += acc[s].z;
+  }
+  *out = make_float2(t.x / t.z, t.y / t.z);
+  if (lane == 0) a.lse_out[at] = M + __logf(t.z);
+}
+
+// A fused step's bookkeeping for workgroup b of num_seqs: sequence b's tail
+// moves past its new token (or raises the append's flag); with RECORDS, the
+// routes that no valid CSR row lists under their own sequence, which no merge
+// workgroup is sure to visit, have their records combined here.
+template <int WAVES, bool RECORDS>
+__device__ __forceinline__ void step_bookkeeping(const MergeArgs& a, int b, int lane, int wave) {
+  if (threadIdx.x == 0) {
     int r = 0;
     const int st = tail_append_status(a, b, r);
     if (st == 1)
@@ -1075,69 +1362,88 @@ __global__ __launch_bounds__(64) void merge_kernel(MergeArgs a) {
     else if (st)
       atomicOr(a.err_flags, st >> 8);
   }
+  if constexpr (RECORDS) {
+    for (int64_t base = 64 * ((int64_t)b * WAVES + wave); base < a.num_routes;
+         base += 64 * (int64_t)a.num_seqs * WAVES) {
+      const int u = (int)base + lane;
+      bool orphan = false;
+      if (u < a.num_routes) {
+        const int seq = a.routes[u].seq;
+        orphan = seq < 0 || seq >= a.num_seqs;
+        if (!orphan) {
+          const int r0 = a.seq_route_begin[seq], r1 = a.seq_route_begin[seq + 1];
+          orphan = r0 < 0 || r1 > a.num_routes || u < r0 || u >= r1;
+        }
+      }
+      for (uint64_t left = __ballot(orphan); left; left &= left - 1) {
+        const int r = (int)base + __builtin_ctzll(left);
+        for (int h = 0; h < a.num_q_heads; ++h) {
+          float2 o;
+          float lse;
+          if (combine_unit<1>(a.rec, pieces_of(a.rec, r, h), lane, wave, nullptr, o, lse))
+            store_row(a.rec, r, h, lane, o, lse);
+        }
+      }
+    }
+  }
+}
+
+// Merge of sequence blockIdx.y's query head blockIdx.x by WAVES waves.  A
+// fused step has one more workgroup per sequence, for its bookkeeping.  With
+// RECORDS (a fused step of a split launch) the workgroup first combines its
+// rows' records; up to kLdsRows rows stay in LDS for the merge.
+template <int WAVES, bool RECORDS>
+__global__ __launch_bounds__(64 * WAVES) void merge_kernel(MergeArgs a) {
+  __shared__ float3 s_sum[WAVES][64];
+  __shared__ float s_max[WAVES];
+  const int h = blockIdx.x, b = blockIdx.y;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int Hq = a.num_q_heads;
+  if (h == Hq) {
+    step_bookkeeping<WAVES, RECORDS>(a, b, lane, wave);
+    return;
+  }
   const int r0 = a.seq_route_begin[b], r1 = a.seq_route_begin[b + 1];
-  float2* out = reinterpret_cast<float2*>(a.out + ((size_t)b * Hq + h) * kDim) + lane;
-  float* lse_out = a.lse_out + (size_t)b * Hq + h;
   if (r0 < 0 || r1 < r0 || r1 > a.num_routes) {
-    *out = make_float2(qnan(), qnan());
-    if (lane == 0) {
-      *lse_out = qnan();
+    if (threadIdx.x < 64)
+      reinterpret_cast<float2*>(a.out + ((size_t)b * Hq + h) * kDim)[lane] =
+          make_float2(qnan(), qnan());
+    if (threadIdx.x == 0) {
+      a.lse_out[(size_t)b * Hq + h] = qnan();
       if (h == 0) atomicOr(a.err_flags, KF_EFLAG_BAD_ROUTE);
     }
     return;
   }
-  constexpr float kLog2e = 1.44269504088896340736f;
-  // lane i reads the lse of routes r0 + i, r0 + i + 64, ...
-  const int n = r1 - r0;
-  float M = neg_inf();
-  bool nan_seen = false;
-  for (int i = lane; i < n; i += 64) {
-    const float l = a.lse_part[(size_t)(r0 + i) * Hq + h];
-    nan_seen |= l != l;
-    M = fmaxf(M, l);
-  }
-  for (int m = 32; m >= 1; m >>= 1) M = fmaxf(M, __shfl_xor(M, m));
-  const bool any_nan = __ballot(nan_seen) != 0;
-  if (any_nan || M == neg_inf()) {
-    const float v = any_nan ? qnan() : 0.0f;
-    *out = make_float2(v, v);
-    if (lane == 0) *lse_out = any_nan ? qnan() : neg_inf();
-    return;
-  }
-  // routes in order; route base + j's weight comes from lane j
-  float L = 0.0f, o0 = 0.0f, o1 = 0.0f;
-  for (int base = 0; base < n; base += 64) {
-    const int i = base + lane;
-    const float wl = i < n ? exp2_fast((a.lse_part[(size_t)(r0 + i) * Hq + h] - M) * kLog2e) : 0.0f;
-    const int cnt = min(64, n - base);
-    const float2* ob = reinterpret_cast<const float2*>(a.o_part + ((size_t)(r0 + base) * Hq + h) * kDim) + lane;
-    const size_t rs = (size_t)Hq * kDim / 2;  // float2 elements from one route's row to the next
-    int j = 0;
-    for (; j + 4 <= cnt; j += 4) {  // four routes' loads in flight, summed in route order
-      float wr[4];
-      float2 v[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        wr[k] = __shfl(wl, j + k);
-        v[k] = ob[(j + k) * rs];
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        L += wr[k];
-        o0 += wr[k] * v[k].x;
-        o1 += wr[k] * v[k].y;
+  if constexpr (RECORDS) {
+    __shared__ float2 s_row[kLdsRows][64];
+    __shared__ float2 s_rec[WAVES][64];
+    __shared__ float s_lse[kLdsRows];
+    const int n = r1 - r0;
+    const bool share = WAVES == 4 && n == 1;  // one row: the waves share its records
+    for (int i = share ? 0 : wave; i < n; i += share ? 1 : WAVES) {
+      const size_t row = (size_t)(r0 + i) * Hq + h;
+      // a whole unit's row is in place; its loads go out with the records'
+      float2 o = reinterpret_cast<const float2*>(a.o_part)[row * (kDim / 2) + lane];
+      float lse = a.lse_part[row];
+      const Pieces p = pieces_of(a.rec, r0 + i, h);
+      const bool got = WAVES == 4 && share
+                           ? combine_unit<WAVES>(a.rec, p, lane, wave, s_rec, o, lse)
+                           : combine_unit<1>(a.rec, p, lane, wave, s_rec, o, lse);
+      if (share && wave != 0) continue;
+      if (got) store_row(a.rec, r0 + i, h, lane, o, lse);
+      if (n <= kLdsRows) {
+        s_row[i][lane] = o;
+        if (lane == 0) s_lse[i] = lse;
       }
     }
-    for (; j < cnt; ++j) {
-      const float wr = __shfl(wl, j);
-      const float2 v = ob[j * rs];
-      L += wr;
-      o0 += wr * v.x;
-      o1 += wr * v.y;
+    if (n <= kLdsRows) {
+      __syncthreads();
+      if (wave == 0) merge_lds_rows(a, b, h, n, lane, s_row, s_lse);
+      return;
     }
+    publish_to_workgroup();  // the rows written above, before the merge reads them
   }
-  *out = make_float2(o0 / L, o1 / L);
-  if (lane == 0) *lse_out = M + __logf(L);
+  merge_rows<WAVES>(a, b, h, r0, r1 - r0, lane, wave, s_sum, s_max);
 }
 
 template <bool FP8, int UPW>
@@ -1148,6 +1454,16 @@ hipError_t launch_partial_kernel(const PartialArgs& a, dim3 grid, hipStream_t st
   else
     hipLaunchKernelGGL(HIP_KERNEL_NAME(partial_kernel<FP8, UPW, false>), grid, dim3(kThreads * UPW), 0,
                        stream, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_combine(const RecordArgs& rec, int num_launch, hipStream_t stream) {
+  if (rec.max_chunks > kChunksOneWave)
+    hipLaunchKernelGGL(combine_kernel<4>, dim3(rec.num_q_heads, num_launch), dim3(kThreads), 0,
+                       stream, rec);
+  else
+    hipLaunchKernelGGL(combine_kernel<1>, dim3((rec.num_q_heads + 3) / 4, num_launch),
+                       dim3(kThreads), 0, stream, rec);
   return hipGetLastError();
 }
 
@@ -1200,6 +1516,7 @@ hipError_t launch_append(const AppendArgs& a, bool fp8, hipStream_t stream) {
 
 hipError_t launch_partial(const PartialArgs& a, bool fp8, hipStream_t stream) {
   if (a.num_units_routes == 0) return hipSuccess;
+  const RecordArgs rec = records_of(a);
   if (!fp8 && a.units_per_wg == 2)
     return launch_partial_kernel<false, 2>(a, dim3(1, a.num_kv_heads, (a.num_units_routes + 1) / 2),
                                            stream);
@@ -1211,10 +1528,8 @@ hipError_t launch_partial(const PartialArgs& a, bool fp8, hipStream_t stream) {
   }
   hipError_t e = fp8 ? launch_partial_kernel<true, 1>(a, grid, stream)
                      : launch_partial_kernel<false, 1>(a, grid, stream);
-  if (e != hipSuccess || a.max_chunks == 1) return e;
-  hipLaunchKernelGGL(combine_kernel, dim3(a.num_kv_heads, a.num_units_routes), dim3(kThreads), 0,
-                     stream, a);
-  return hipGetLastError();
+  if (e != hipSuccess || a.max_chunks == 1 || a.merge_combines) return e;
+  return launch_combine(rec, a.num_units_routes, stream);
 }
 
 hipError_t launch_gather(const PartialArgs& a, bool fp8, int route, int max_tokens, void* out_k,
@@ -1232,7 +1547,16 @@ hipError_t launch_gather(const PartialArgs& a, bool fp8, int route, int max_toke
 
 hipError_t launch_merge(const MergeArgs& a, hipStream_t stream) {
   if (a.num_seqs == 0 || a.num_q_heads == 0) return hipSuccess;
-  hipLaunchKernelGGL(merge_kernel, dim3(a.num_q_heads, a.num_seqs), dim3(64), 0, stream, a);
+  const dim3 grid(a.num_q_heads + (a.tail_route ? 1 : 0), a.num_seqs);
+  const int rows = a.num_routes / a.num_seqs;  // mean rows per sequence
+  if (a.rec.ml && (rows > 0 ? rows : 1) * a.rec.max_chunks <= kRecordsOneWave)
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(merge_kernel<1, true>), grid, dim3(64), 0, stream, a);
+  else if (a.rec.ml)
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(merge_kernel<4, true>), grid, dim3(256), 0, stream, a);
+  else if (rows >= kMergeRowsFourWaves)
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(merge_kernel<4, false>), grid, dim3(256), 0, stream, a);
+  else
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(merge_kernel<1, false>), grid, dim3(64), 0, stream, a);
   return hipGetLastError();
 }
 
