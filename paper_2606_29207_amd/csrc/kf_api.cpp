@@ -200,6 +200,77 @@ int32_t units_per_workgroup(bool fp8, bool route_list, const ChunkPlan& plan, in
              : 1;
 }
 
+// Whether a launch of num_launch routes runs as spans, whatever its workspace.
+// Measured against the chunk plan, both with the combining merge, one box:
+//  - Ragged tables: 4-16 sequences of 300-4000 tokens and 8 KV heads -29 to
+//    -37% (48.2 -> 36.7 us at 139 MB, fp8 42.2 -> 30.0 us), 64 of 300-3000
+//    -20%, 12 of 20000-60000 -9 to -26%, 192 of 65-1100 -5 to -16%, the
+//    agentic batch (1208 units, 7.7 GB) -1.5%; the one larger batch that lost
+//    did so by 1.6% (256 of 300-6000 tokens, 2.0 GB).  Below two tiles per
+//    wave the parts cost more than the balance gives (8 sequences of 300-3000
+//    tokens 20.2 -> 22.0 us), and so they do with routes of at most 32 pages
+//    and more than 8 query heads per KV head (250 of 100-260 tokens, 16 heads:
+//    46.5 -> 49.0 us).
+//  - Equal tables whose chunk plan keeps units whole (they fill the GPU
+//    evenly, or are short) stay as they are: 2000 fp8 units of 44 or 125 pages
+//    lose 5-7%, 512 units 1-4%.  Split ones run as spans when units outnumber
+//    the slots (640 to 3000 units, 44 to 375 pages: bf16 -1 to -15%, fp8 0 to
+//    -30%), or the compute units without their ranges filling them evenly
+//    (400 units: -2 to -18%; 320 and 384 units, whose ranges do, -4 to +3%).
+// Launches over a route list keep the chunk plan: the page table does not
+// describe their routes.
+namespace {
+bool span_launch(int32_t num_launch, int32_t num_kv_heads, int32_t group,
+                 int32_t max_pages_per_route, int32_t num_page_ids, bool fp8, bool listed,
+                 const ChunkPlan& plan, int64_t slots) {
+  if (listed || num_launch <= 0 || num_launch > kSpanRoutes) return false;
+  const int64_t tile = fp8 ? 4 : 2, units = (int64_t)num_launch * num_kv_heads;
+  if (num_launch * (((int64_t)max_pages_per_route + tile - 1) / tile) > INT32_MAX) return false;
+  if ((int64_t)num_page_ids * num_kv_heads < 2 * tile * slots * kWaves) return false;
+  if (ragged_table(num_page_ids, num_launch, max_pages_per_route))
+    return max_pages_per_route > 32 || group <= 8;
+  return plan.max_chunks > 1 &&
+         (units > slots || (units > slots / 2 && units * plan.max_chunks % (slots / 2) != 0));
+}
+}  // namespace
+
+SpanPlan plan_span(int32_t num_launch, int32_t num_kv_heads, int32_t group,
+                   int32_t max_pages_per_route, int32_t num_page_ids, bool fp8, bool listed,
+                   const ChunkPlan& plan, int64_t slots) {
+  if (span_lds_bytes(group, num_launch) > kSpanLds ||
+      !span_launch(num_launch, num_kv_heads, group, max_pages_per_route, num_page_ids, fp8, listed,
+                   plan, slots))
+    return SpanPlan{};
+  // The records have to fit what both a workspace of the queried size and the
+  // library's scratch array are sure to hold, so that kf_decode_step and
+  // kf_decode_step_no_alloc take the same path: the chunk plans of this many
+  // routes, and of the most routes below one round of units.
+  size_t sure = 0;
+  const int64_t below = (slots - 1) / num_kv_heads;
+  for (const int64_t m : {(int64_t)num_launch, below < num_launch ? below : (int64_t)num_launch})
+    for (const bool ragged : {false, true}) {
+      const ChunkPlan c = plan_for_slots((int32_t)m, num_kv_heads, max_pages_per_route, ragged,
+                                         fp8, slots, false);
+      const size_t t = workspace_layout((int32_t)m, num_kv_heads, group, c.max_chunks,
+                                        ordered_dispatch(c, (int32_t)m, num_kv_heads, slots))
+                           .total;
+      if (t > sure) sure = t;
+    }
+  if (sure > KF_SCRATCH_BYTES) sure = KF_SCRATCH_BYTES;
+  // One resident round of workgroups, or down to 3/4 of one if that fits.
+  const int64_t want = slots / num_kv_heads > 1 ? slots / num_kv_heads : 1;
+  for (int64_t wg = want; wg * 4 >= want * 3; --wg) {
+    SpanPlan p{};
+    const size_t recs = (size_t)(wg + (wg < num_launch ? wg : num_launch)) * num_kv_heads * group;
+    p.ml_off = round_up((size_t)num_launch * 2 * sizeof(int32_t), 256);
+    p.o_off = p.ml_off + round_up(recs * 2 * sizeof(float), 256);
+    p.total = p.o_off + round_up(recs * kDim * sizeof(float), 256);
+    p.wg_cols = (int32_t)wg;
+    if (p.total <= sure) return p;
+  }
+  return SpanPlan{};
+}
+
 // The merge of a fused step also combines a split launch's records unless a
 // sequence may hold so many routes that its one workgroup per head would
 // take them one after another for too long.  Merged: chat batches (8
@@ -391,6 +462,15 @@ int prepare_partial(const kf_shape* shape, const void* q, const void* k_pool, co
   a.ws_ml = reinterpret_cast<float*>(ws + l.ml_off);
   a.ws_o = reinterpret_cast<float*>(ws + l.o_off);
   a.order = ordered ? reinterpret_cast<uint32_t*>(ws + l.order_off) : nullptr;
+  const kf::SpanPlan sp = kf::plan_span(
+      num_launch, shape->num_kv_heads, group, max_pages_per_route, shape->num_page_ids, fp8,
+      route_list != nullptr, plan, 2 * (int64_t)kf::cu_count());
+  if (sp.wg_cols > 0 && sp.total <= workspace_bytes) {
+    a.span_cols = sp.wg_cols * kf::kWaves;
+    a.span_table = reinterpret_cast<int32_t*>(ws);
+    a.span_ml = reinterpret_cast<float*>(ws + sp.ml_off);
+    a.span_o = reinterpret_cast<float*>(ws + sp.o_off);
+  }
   a.err_flags = err_flags;
   a.num_seqs = shape->num_seqs;
   a.num_q_heads = shape->num_q_heads;
@@ -496,6 +576,12 @@ int decode_step_impl(const kf_shape* shape, const void* q, void* k_pool, void* v
     pa.ws_o = reinterpret_cast<float*>(b + (reinterpret_cast<uintptr_t>(pa.ws_o) - s0));
     if (pa.order)
       pa.order = reinterpret_cast<uint32_t*>(b + (reinterpret_cast<uintptr_t>(pa.order) - s0));
+    if (pa.span_table) {
+      pa.span_table =
+          reinterpret_cast<int32_t*>(b + (reinterpret_cast<uintptr_t>(pa.span_table) - s0));
+      pa.span_ml = reinterpret_cast<float*>(b + (reinterpret_cast<uintptr_t>(pa.span_ml) - s0));
+      pa.span_o = reinterpret_cast<float*>(b + (reinterpret_cast<uintptr_t>(pa.span_o) - s0));
+    }
   }
   const hipStream_t s = as_stream(stream);
   const bool fp8 = shape->kv_dtype == KF_KV_FP8_E4M3;
@@ -515,7 +601,7 @@ int decode_step_impl(const kf_shape* shape, const void* q, void* k_pool, void* v
   ma.page_ids = page_ids;
   ma.num_pages = shape->num_pages;
   ma.num_page_ids = shape->num_page_ids;
-  if (pa.max_chunks > 1 && kf::merge_combines(num_routes, shape->num_seqs)) {
+  if ((pa.max_chunks > 1 || pa.span_cols) && kf::merge_combines(num_routes, shape->num_seqs)) {
     pa.merge_combines = 1;
     ma.rec = kf::records_of(pa);
   }

@@ -22,6 +22,9 @@ constexpr int kMaxLaunchRoutes = 65535;  // routes per launch and KV heads: grid
 constexpr int kChunksOneWave = 8;        // ranges per unit up to which one wave combines a head
 constexpr int kRecordsOneWave = 8;       // mean records per (sequence, head) up to which one wave merges them
 constexpr int kLdsRows = 16;             // rows per sequence that a combining merge keeps in LDS
+constexpr int kLdsStride = kDim + 4;     // padded row of an output buffer in LDS
+constexpr int kSpanRoutes = 1024;        // most routes of a span launch (its table in LDS)
+constexpr size_t kSpanLds = 80 << 10;    // most LDS of its workgroups: two per compute unit
 constexpr int kMergeRowsFourWaves = 8;   // mean rows per sequence from which four waves merge a head
 constexpr int kOrderBuckets = 64;        // range-size classes of the dispatch order
 constexpr int64_t kMaxOrderItems = int64_t(1) << 20;  // largest split launch given a dispatch order
@@ -50,6 +53,8 @@ struct RecordArgs {
   const int32_t* route_list;  // as in PartialArgs
   int32_t num_routes, num_q_heads, num_kv_heads, group;
   int32_t max_chunks;
+  int32_t places;             // record places per (route, head): all of them, or a span's mean
+  const int32_t* span_table;  // records of a span launch (NULL: of chunks)
 };
 
 struct PartialArgs {
@@ -70,6 +75,12 @@ struct PartialArgs {
   int32_t num_routes, max_pages_per_route;
   int32_t num_units_routes;  // routes launched: num_list, or num_routes without a list
   int32_t chunk_pages, max_chunks;  // a unit of n pages uses ceil(n / chunk_pages) workgroups
+  // Span launch (span_cols wave columns; 0: none): its table and its records
+  // ([span places][Hkv][G]) in the workspace.
+  int32_t span_cols;
+  int32_t* span_table;
+  float* span_ml;
+  float* span_o;
   int32_t merge_combines;  // the merge kernel of a fused step combines the records
   int32_t units_per_wg;  // 2: unsplit bf16 launch, two units per 512-thread workgroup
   // Split launches of several rounds: the dispatch order of the work items,
@@ -111,8 +122,16 @@ struct MergeArgs {
 };
 
 inline RecordArgs records_of(const PartialArgs& a) {
-  return {a.ws_ml, a.ws_o, a.o_part, a.lse_part, a.route_list, a.num_routes, a.num_q_heads,
-          a.num_kv_heads, a.group, a.max_chunks};
+  const bool span = a.span_cols > 0;
+  return {span ? a.span_ml : a.ws_ml, span ? a.span_o : a.ws_o, a.o_part, a.lse_part, a.route_list,
+          a.num_routes, a.num_q_heads, a.num_kv_heads, a.group, a.max_chunks,
+          span ? 1 + a.span_cols / kWaves / a.num_units_routes : a.max_chunks,
+          span ? a.span_table : nullptr};
+}
+
+// LDS of a span workgroup: the parts of its columns and the route table.
+inline size_t span_lds_bytes(int32_t group, int32_t num_launch) {
+  return sizeof(float) * ((size_t)2 * kWaves * group * (kLdsStride + 2) + 4 * (size_t)num_launch + 1);
 }
 
 struct WorkspaceLayout {
@@ -151,6 +170,16 @@ int32_t units_per_workgroup(bool fp8, bool route_list, const ChunkPlan& plan, in
 // Whether the merge kernel of a fused step also combines the records of a
 // split launch.
 bool merge_combines(int32_t num_routes, int32_t num_seqs);
+// Span launch of num_launch routes: workgroup columns (0: not a span launch)
+// and the workspace it uses.  plan: the launch's chunk plan, which it keeps
+// when its workspace is too small for the spans.
+struct SpanPlan {
+  int32_t wg_cols;
+  size_t ml_off, o_off, total;  // the table comes first
+};
+SpanPlan plan_span(int32_t num_launch, int32_t num_kv_heads, int32_t group,
+                   int32_t max_pages_per_route, int32_t num_page_ids, bool fp8, bool listed,
+                   const ChunkPlan& plan, int64_t slots);
 // A split launch of at least two rounds of the GPU's `slots` resident
 // workgroups (and at most kMaxOrderItems work items) runs its work items
 // in a computed order, largest ranges first (order_kernel).

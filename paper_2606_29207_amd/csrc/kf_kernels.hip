@@ -59,7 +59,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kLn2 = 0.69314718055994530942f;
 constexpr int kThreads = kWaves * 64;
-constexpr int kLdsStride = kDim + 4;  // padded row of the per-wave output buffer
 
 
 __device__ __forceinline__ float neg_inf() { return -__builtin_inff(); }
@@ -488,7 +487,13 @@ __device__ __forceinline__ void reset(Attn& s) {
 // the page's K scale), vs: V scale, of the lane's page; tok0: the lane's
 // first route-local token, lim: the token bound.  MASK: the tile can hold
 // slots past the bound; their V bits are zeroed and they add nothing.
-template <bool FP8, bool MASK>
+// TILE_SUM: the tile's p.V is summed from zero and then added, one rounding of
+// the running output per tile instead of two: a bf16 span wave's chains
+// are several times as long as a chunk wave's, and its error stays at theirs
+// (agentic batch 9.6e-7 against 8.9e-7; 1.1e-6 without).  The add takes the
+// place of the rescaling product, so it costs no time; fp8 tiles have no
+// registers to spare for it, and their error is the bf16 pair's (5e-6).
+template <bool FP8, bool MASK, bool TILE_SUM = false>
 __device__ __forceinline__ void attend(const TileRaw<FP8>& t, const u32x4 (&qb)[4], float ks,
                                        float vs, int tok0, int lim, Attn& st) {
   constexpr int NC = Geo<FP8>::NC, NH = Geo<FP8>::NH;
@@ -525,8 +530,10 @@ __device__ __forceinline__ void attend(const TileRaw<FP8>& t, const u32x4 (&qb)[
   const float alpha = exp2_fast(st.m - m_new);
   st.m = m_new;
   st.l *= alpha;
+  if constexpr (!TILE_SUM) {
 #pragma unroll
-  for (int b8 = 0; b8 < 8; ++b8) st.o[b8] *= alpha;
+    for (int b8 = 0; b8 < 8; ++b8) st.o[b8] *= alpha;
+  }
 
   // ---- P^T operands: half h2 holds slots 8*h2 + j (j < 8) of the lane's
   // range, i.e. MFMA c = 2*h2 + j/4, row r4 = j%4; bf16 hi + lo
@@ -573,10 +580,20 @@ __device__ __forceinline__ void attend(const TileRaw<FP8>& t, const u32x4 (&qb)[
 #pragma unroll
         for (int wd = 0; wd < 4; ++wd) vr[h2][wd] &= msk[h2][wd];
     }
+    if constexpr (TILE_SUM) {
+      f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int h2 = 0; h2 < NH; ++h2) {
-      st.o[b8] = mfma16(vr[h2], phi[h2], st.o[b8]);
-      st.o[b8] = mfma16(vr[h2], plo[h2], st.o[b8]);
+      for (int h2 = 0; h2 < NH; ++h2) sum = mfma16(vr[h2], plo[h2], sum);
+#pragma unroll
+      for (int h2 = 0; h2 < NH; ++h2) sum = mfma16(vr[h2], phi[h2], sum);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) st.o[b8][k] = __builtin_fmaf(st.o[b8][k], alpha, sum[k]);
+    } else {
+#pragma unroll
+      for (int h2 = 0; h2 < NH; ++h2) {
+        st.o[b8] = mfma16(vr[h2], phi[h2], st.o[b8]);
+        st.o[b8] = mfma16(vr[h2], plo[h2], st.o[b8]);
+      }
     }
   }
 }
@@ -936,6 +953,505 @@ __global__ __launch_bounds__(kThreads * UPW, 2 / UPW) void partial_kernel(Partia
   }
 }
 
+// ------------------------------------------------------------------- spans
+// A span launch cuts the whole launch's tiles, and not each unit's pages,
+// into equal parts: the tiles of all routes, route after route, are split
+// into `cols` columns of equal length, and wave (column, KV head) streams its
+// column's tiles of that head, whatever routes they belong to.  One resident
+// round of workgroups (two per compute unit) then carries a ragged batch
+// without empty, short or late workgroups, and a wave starts once and keeps
+// its two tiles in flight across routes.  The four waves of a workgroup hold
+// four columns in a row of one KV head.  A wave writes a route that lies
+// inside its column straight to o_part; the parts of routes that its column
+// cuts go to LDS, where the workgroup joins parts of one route, and only
+// routes cut by a workgroup's bounds leave records (place: workgroup column +
+// launch position) for the combine.
+//
+// A cut route's parts are kept in workgroup-column order: with c0 the column
+// of its first part, the part of workgroup column c of launch position u has
+// record place c + min(u, c0).  The places of two routes never meet: the next
+// cut route begins in the column where this one ends, or later, and both u
+// and c0 grow by at least one.  Table in the workspace, for the combine: two
+// words per launch position, the place of its first record and its number of
+// records (0: the outputs are in place).
+struct SpanCols {
+  int q, rem, cols;  // the first rem columns hold q + 1 tiles, the others q
+  __device__ __forceinline__ int begin(int c) const { return c * q + min(c, rem); }
+  __device__ __forceinline__ int of(int t) const {
+    const int edge = rem * (q + 1);
+    return t < edge ? t / (q + 1) : rem + (t - edge) / q;
+  }
+};
+
+__device__ __forceinline__ SpanCols span_cols(int tiles, int cols) {
+  return {tiles / cols, tiles % cols, cols};
+}
+
+// One tile of a wave's walk (wave-uniform): the route's tokens from the tile's
+// first one on, its launch position and marks, its page ids.
+struct SpanTile {
+  int left;
+  uint32_t uf;  // launch position and marks: kSpanLast ends its part, kSpanToken takes the step's
+                // token, kSpanBad has a page id outside the pool
+  int pid0, pid1, pid2, pid3;
+};
+constexpr uint32_t kSpanToken = 1u << 29, kSpanLast = 1u << 30, kSpanBad = 1u << 31;
+
+// A tile with slots past the route: their V bits zeroed (such slots may hold
+// anything), and for fp8 the V scale of a page wholly past it.  tok: the
+// lane's first token within the tile.
+template <bool FP8>
+__device__ __forceinline__ void mask_tile(TileRaw<FP8>& t, int tok, int left) {
+  u32x4 msk;
+#pragma unroll
+  for (int wd = 0; wd < 4; ++wd) {
+    uint32_t m = 0;
+    constexpr int N = FP8 ? 4 : 2;  // slots per dword
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      m |= tok + N * wd + k < left ? (FP8 ? 0xFFu << (8 * k) : 0xFFFFu << (16 * k)) : 0u;
+    msk[wd] = m;
+  }
+#pragma unroll
+  for (int b8 = 0; b8 < 8; ++b8) t.v[b8] &= msk;
+  if constexpr (FP8) t.vs = tok < left ? t.vs : 0.0f;
+}
+
+// The step's token of (route, KV head g) written by one wave (the fused
+// append of store_new_token): loaded first, stored later.  Lane: dims 2*lane
+// and 2*lane + 1.
+struct WaveToken {
+  uint32_t k2, v2;
+  float ks, vs;         // fp8: the page's scales
+  E4m3Slots k_at, v_at; // fp8: the page's slots, in case the token re-encodes them
+  int pid, slot;
+};
+
+template <bool FP8>
+__device__ __forceinline__ WaveToken load_wave_token(const PartialArgs& a, int seq, int pid,
+                                                     int slot, int g, int lane) {
+  const size_t tok = ((size_t)seq * a.num_kv_heads + g) * kDim;
+  WaveToken t;
+  t.k2 = reinterpret_cast<const uint32_t*>(a.k_new + tok)[lane];
+  t.v2 = reinterpret_cast<const uint32_t*>(a.v_new + tok)[lane];
+  t.ks = t.vs = 1.0f;
+  if constexpr (FP8) {
+    t.ks = a.k_scale[(size_t)pid * a.num_kv_heads + g];
+    t.vs = a.v_scale[(size_t)pid * a.num_kv_heads + g];
+    const size_t at = pool_slice(pid, g, a.num_kv_heads, a.num_pages, a.head_major) * (kPage * kDim);
+    t.k_at = load_e4m3_slots(static_cast<const uint8_t*>(a.k_pool) + at, false, lane);
+    t.v_at = load_e4m3_slots(static_cast<const uint8_t*>(a.v_pool) + at, true, lane);
+  }
+  t.pid = pid;
+  t.slot = slot;
+  return t;
+}
+
+template <bool FP8>
+__device__ __forceinline__ void store_wave_token(const PartialArgs& a, const WaveToken& t, int g,
+                                                 int lane) {
+  const int H = a.num_kv_heads;
+  const size_t head = pool_slice(t.pid, g, H, a.num_pages, a.head_major);
+  if constexpr (!FP8) {
+    reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(a.k_pool_w) +
+                                (head * kPage + t.slot) * kDim)[lane] = t.k2;
+    uint16_t* vp = static_cast<uint16_t*>(a.v_pool_w) + (head * kDim + 2 * lane) * kPage + t.slot;
+    vp[0] = (uint16_t)t.v2;
+    vp[kPage] = (uint16_t)(t.v2 >> 16);
+  } else {
+    const float k_s = append_e4m3_head(static_cast<uint8_t*>(a.k_pool_w) + head * (kPage * kDim),
+                                       t.ks, t.slot, false, t.k2, lane, &t.k_at);
+    const float v_s = append_e4m3_head(static_cast<uint8_t*>(a.v_pool_w) + head * (kPage * kDim),
+                                       t.vs, t.slot, true, t.v2, lane, &t.v_at);
+    if (lane == 0) {
+      a.k_scale_w[(size_t)t.pid * H + g] = k_s;
+      a.v_scale_w[(size_t)t.pid * H + g] = v_s;
+    }
+  }
+}
+
+// Constant-address-space view of a table that the kernel does not write:
+// uniform reads stay scalar loads beside the kernel's stores.
+typedef const int32_t __attribute__((address_space(4)))* const_i32;
+__device__ __forceinline__ const_i32 as_const(const int32_t* p) { return (const_i32)(uintptr_t)p; }
+
+template <bool FP8, bool HM>
+__global__ __launch_bounds__(kThreads, 2) void span_kernel(PartialArgs a) {
+  using GeoT = Geo<FP8>;
+  constexpr int TP = GeoT::TP, NC = GeoT::NC;
+  extern __shared__ f32x4 s_lds[];
+  float* s_dyn = reinterpret_cast<float*>(s_lds);  // parts: [2 * kWaves][G][kLdsStride], (max, sum)
+  __shared__ int s_sum[kWaves], s_start[kWaves], s_part[2 * kWaves];
+  const int U = a.num_units_routes, H = a.num_kv_heads, G = a.group, Hq = a.num_q_heads;
+  const int tid = threadIdx.x, lane = tid & 63, grp = lane >> 4, li = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = blockIdx.x % H, blk = blockIdx.x / H;  // KV head, workgroup column
+  const int hq0 = g * G;
+
+  // ---- the route table: first tiles (U + 1), page lists, lengths, sequences
+  int* s_pre = reinterpret_cast<int*>(s_dyn + 2 * kWaves * G * (kLdsStride + 2));
+  int *s_base = s_pre + U + 1, *s_n = s_base + U, *s_seq = s_n + U;
+  constexpr int PER = kSpanRoutes / kThreads;
+  const int per = (U + kThreads - 1) / kThreads;
+  int cnt[PER], sum = 0;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int u = tid * per + i;
+    cnt[i] = 0;
+    if (i < per && u < U) {
+      const int r = a.route_list ? a.route_list[u] : u;
+      RouteView rv{};
+      bool listed = r >= 0 && r < a.num_routes;
+      if (listed) rv = read_route(a, r);
+      if (listed && !rv.bad) cnt[i] = (rv.npages + TP - 1) / TP;
+      s_base[u] = rv.base;
+      s_n[u] = rv.bad && rv.n == 0 ? -1 : rv.n;  // 0: empty
+      s_seq[u] = rv.app ? ~rv.seq : cnt[i] ? rv.seq : 0;
+      if (blockIdx.x == 0 && (!listed || rv.bad)) atomicOr(a.err_flags, KF_EFLAG_BAD_ROUTE);
+      sum += cnt[i];
+    }
+  }
+  int incl = sum;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int v = __shfl_up(incl, d);
+    if (lane >= d) incl += v;
+  }
+  if (lane == 63) s_sum[w] = incl;
+  if (tid < kWaves) s_start[tid] = -1;
+  if (tid < 2 * kWaves) s_part[tid] = -1;
+  __syncthreads();
+  int pre = incl - sum, T = 0;
+#pragma unroll
+  for (int i = 0; i < kWaves; ++i) {
+    if (i < w) pre += s_sum[i];
+    T += s_sum[i];
+  }
+  const SpanCols sc = span_cols(T, max(1, min(a.span_cols, T)));
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int u = tid * per + i;
+    if (i < per && u < U) {
+      s_pre[u] = pre;
+#pragma unroll
+      for (int v = 0; v < kWaves; ++v) {  // the route at the start of each wave's column
+        const int c = blk * kWaves + v, t = sc.begin(c);
+        if (c < sc.cols && pre <= t && t < pre + cnt[i]) s_start[v] = u;
+      }
+      if (blockIdx.x == 0) {
+        const int c0 = cnt[i] ? sc.of(pre) / kWaves : 0;
+        const int c1 = cnt[i] ? sc.of(pre + cnt[i] - 1) / kWaves : 0;
+        a.span_table[2 * u] = c0 + min(u, c0);
+        a.span_table[2 * u + 1] = c1 > c0 ? c1 - c0 + 1 : 0;
+      }
+      pre += cnt[i];
+    }
+  }
+  if (tid == 0) s_pre[U] = T;
+  __syncthreads();
+
+  // ---- outputs of routes without tiles (empty or bad), spread over the workgroups
+  for (int u = blockIdx.x; u < U; u += gridDim.x) {
+    if (s_pre[u + 1] != s_pre[u]) continue;
+    const int r = a.route_list ? a.route_list[u] : u;
+    if (r < 0 || r >= a.num_routes) continue;
+    const bool bad = s_n[u] != 0;
+    const float ov = bad ? qnan() : 0.0f, lv = bad ? qnan() : neg_inf();
+    for (int e = tid; e < Hq * kDim; e += kThreads) a.o_part[(size_t)r * Hq * kDim + e] = ov;
+    for (int h = tid; h < Hq; h += kThreads) a.lse_part[(size_t)r * Hq + h] = lv;
+  }
+
+  // ---- this wave's column
+  const int col = blk * kWaves + w;
+  const int t0 = sc.begin(col), t1 = col < sc.cols ? sc.begin(col + 1) : t0;
+  auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+  const const_i32 page_ids = as_const(a.page_ids);
+  // The fused step's tokens, for the routes that end inside this column (and
+  // bad routes there, whose pools take theirs all the same; column 0 has
+  // those before the first tile).  Each is loaded while the one before it is
+  // stored, and stored before the loads of the tile that holds its page,
+  // which see the wave's own stores: bf16 tokens right before that tile, fp8
+  // ones, which may re-encode their page, before the column's first tile.
+  WaveToken tok;
+  int tok_u = a.tail_route && (t1 > t0 || col == 0) ? (col == 0 ? 0 : uni(s_start[w])) : U;
+  auto next_token = [&](bool tiles) -> bool {  // tiles: of routes with tiles, or of bad ones
+    for (; tok_u < U; ++tok_u) {
+      const int e = uni(s_pre[tok_u + 1]);
+      if (e > t1) return false;
+      const int sq = uni(s_seq[tok_u]), at = uni(s_n[tok_u]) - 1;
+      if (sq >= 0 || (!FP8 && (e > uni(s_pre[tok_u])) != tiles)) continue;
+      tok = load_wave_token<FP8>(a, ~sq, page_ids[uni(s_base[tok_u]) + at / kPage], at % kPage, g,
+                                 lane);
+      ++tok_u;
+      return true;
+    }
+    return false;
+  };
+  {
+    const int from = tok_u;
+    for (bool any = next_token(false); any;) {
+      const WaveToken x = tok;
+      any = next_token(false);
+      store_wave_token<FP8>(a, x, g, lane);
+    }
+    if constexpr (FP8) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    } else {
+      tok_u = from;
+      next_token(true);
+    }
+  }
+  if (t1 > t0) {
+    int u = uni(s_start[w]);
+    int tbeg = uni(s_pre[u]), tend = uni(s_pre[u + 1]), base = uni(s_base[u]), n = uni(s_n[u]);
+    bool app = uni(s_seq[u]) < 0;
+
+    int t = t0;
+    auto tile_info = [&]() -> SpanTile {  // the cursor's tile
+      SpanTile x;
+      const int p0 = (t - tbeg) * TP, np = (n + kPage - 1) / kPage;
+      x.left = n - p0 * kPage;
+      x.uf = (uint32_t)u | (t + 1 == tend || t + 1 == t1 ? kSpanLast : 0u) |
+             (app && t + 1 == tend ? kSpanToken : 0u);
+      auto page_at = [&](int pg) -> int {  // pages past the route read page 0 and are masked
+        const bool in = pg < np;
+        int v = page_ids[base + (in ? pg : 0)];
+        v = in ? v : 0;
+        if ((uint32_t)v >= (uint32_t)a.num_pages) {
+          x.uf |= kSpanBad;
+          v = 0;
+        }
+        return v;
+      };
+      x.pid0 = page_at(p0);
+      x.pid1 = page_at(p0 + 1);
+      x.pid2 = TP > 2 ? page_at(p0 + 2) : 0;
+      x.pid3 = TP > 2 ? page_at(p0 + 3) : 0;
+      return x;
+    };
+    auto advance = [&]() {  // to the next tile, if the column has one
+      if (t + 1 >= t1) return;
+      ++t;
+      if (t == tend) {
+        do ++u;
+        while (uni(s_pre[u + 1]) == t);
+        tbeg = t;
+        tend = uni(s_pre[u + 1]);
+        base = uni(s_base[u]);
+        n = uni(s_n[u]);
+        app = uni(s_seq[u]) < 0;
+      }
+    };
+
+    const int kpage = GeoT::kpage(li), vpage = GeoT::vpage(grp);
+    const size_t head_elems = (size_t)kPage * kDim;
+    const int koff = GeoT::kslot0(li) * kDim + (FP8 ? 16 : 8) * grp;
+    const int voff = li * kPage + GeoT::vslot0(grp);
+    auto issue = [&](TileRaw<FP8>& x, const SpanTile& ti) {
+      if (!FP8 && (ti.uf & kSpanToken)) {
+        store_wave_token<FP8>(a, tok, g, lane);
+        next_token(true);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+      }
+      const int pk = pick4(ti.pid0, ti.pid1, ti.pid2, ti.pid3, kpage);
+      const int pv = pick4(ti.pid0, ti.pid1, ti.pid2, ti.pid3, vpage);
+      const size_t hk = (HM ? (size_t)g * a.num_pages + pk : (size_t)pk * H + g) * head_elems;
+      const size_t hv = (HM ? (size_t)g * a.num_pages + pv : (size_t)pv * H + g) * head_elems;
+      if constexpr (!FP8) {
+        const uint16_t* kb = static_cast<const uint16_t*>(a.k_pool) + hk + koff;
+        const uint16_t* vb = static_cast<const uint16_t*>(a.v_pool) + hv + voff;
+#pragma unroll
+        for (int cc = 0; cc < NC; ++cc)
+#pragma unroll
+          for (int kk = 0; kk < 4; ++kk) x.k[cc][kk] = ld16_stream(kb + cc * 4 * kDim + 32 * kk);
+#pragma unroll
+        for (int b8 = 0; b8 < 8; ++b8) x.v[b8] = ld16_stream(vb + b8 * 16 * kPage);
+      } else {
+        const uint8_t* kb = static_cast<const uint8_t*>(a.k_pool) + hk + koff;
+        const uint8_t* vb = static_cast<const uint8_t*>(a.v_pool) + hv + voff;
+#pragma unroll
+        for (int cc = 0; cc < NC; ++cc)
+#pragma unroll
+          for (int pp = 0; pp < 2; ++pp) x.k[cc][pp] = ld16_stream(kb + cc * 4 * kDim + 64 * pp);
+#pragma unroll
+        for (int b8 = 0; b8 < 8; ++b8) x.v[b8] = ld16_stream(vb + b8 * 16 * kPage);
+        x.ks = a.k_scale[(size_t)pv * H + g];
+        x.vs = a.v_scale[(size_t)pv * H + g];
+      }
+    };
+    u32x4 qb[4];
+    auto load_q = [&](const SpanTile& ti) {
+      const int s0 = uni(s_seq[ti.uf & 0xFFFFu]), sq = s0 < 0 ? ~s0 : s0;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        const int d0 = FP8 ? 64 * (kk >> 1) + 16 * grp + 8 * (kk & 1) : 32 * kk + 8 * grp;
+        qb[kk] = li < G ? ld16(a.q + ((size_t)sq * Hq + hq0 + li) * kDim + d0) : u32x4{0, 0, 0, 0};
+      }
+    };
+
+    Attn acc;
+    reset(acc);
+    uint32_t marks = 0;  // of the part's tiles
+    const int tok0 = vpage * kPage + GeoT::vslot0(grp);  // the lane's first token within a tile
+    auto compute = [&](TileRaw<FP8>& x, const SpanTile& ti) {
+      if (ti.left < TP * kPage) mask_tile<FP8>(x, tok0, ti.left);
+      float ks = a.scale_log2, vs = 1.0f;
+      if constexpr (FP8) {
+        ks *= x.ks;
+        vs = x.vs;
+      }
+      marks |= ti.uf;
+      attend<FP8, false, !FP8>(x, qb, ks, vs, tok0, ti.left, acc);
+    };
+    // end of a part: write the route, or hand the part to the workgroup
+    auto finish = [&](const SpanTile& ti) {
+      float l = acc.l;
+      l += __shfl_xor(l, 16);
+      l += __shfl_xor(l, 32);
+      float m = acc.m;
+      const int pu = ti.uf & 0xFFFFu, pb = uni(s_pre[pu]), pe = uni(s_pre[pu + 1]);
+      if (marks & kSpanBad) {  // a bad page poisons the route
+        m = qnan();
+        if (lane == 0) atomicOr(a.err_flags, KF_EFLAG_BAD_PAGE);
+      }
+      if (pb >= t0 && pe <= t1) {
+        const int r = a.route_list ? as_const(a.route_list)[pu] : pu;
+        const size_t row = (size_t)r * Hq + hq0 + li;
+        if (li < G) {
+          const float lw = m != m ? qnan() : l;
+#pragma unroll
+          for (int b8 = 0; b8 < 8; ++b8) {
+            f32x4 o = acc.o[b8];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) o[k] /= lw;
+            *reinterpret_cast<f32x4*>(a.o_part + row * kDim + 16 * b8 + 4 * grp) = o;
+          }
+          if (grp == 0) a.lse_part[row] = (m + __log2f(l)) * kLn2;
+        }
+      } else {
+        const int slot = 2 * w + (pe > t1 ? 1 : 0);
+        if (li < G) {
+          float* o = s_dyn + (slot * G + li) * kLdsStride;
+#pragma unroll
+          for (int b8 = 0; b8 < 8; ++b8)
+            *reinterpret_cast<f32x4*>(o + 16 * b8 + 4 * grp) = acc.o[b8];
+          if (grp == 0) {
+            float* ml = s_dyn + 2 * kWaves * G * kLdsStride + (slot * G + li) * 2;
+            ml[0] = m;
+            ml[1] = l;
+          }
+        }
+        if (lane == 0) s_part[slot] = pu;
+      }
+      reset(acc);
+      marks = 0;
+    };
+
+    // ---- two register buffers, as in partial_kernel; the tile in flight may
+    // belong to the next route
+    TileRaw<FP8> ra, rb;
+    SpanTile ia = tile_info();
+    load_q(ia);
+    issue(ra, ia);
+    int left = t1 - t0 - 1;  // tiles after the one in hand
+    advance();
+    SpanTile ib = tile_info();
+    bool final_in_b = false;
+    auto one = [&](TileRaw<FP8>& x, const SpanTile& ti, const SpanTile& next) {
+      compute(x, ti);
+      if (ti.uf & kSpanLast) {
+        load_q(next);  // on its way while the part ends
+        finish(ti);
+      }
+    };
+    while (true) {
+      if (left == 0) break;
+      issue(rb, ib);
+      --left;
+      advance();
+      const SpanTile in = tile_info();
+      __builtin_amdgcn_sched_barrier(0);
+      one(ra, ia, ib);
+      if (left == 0) {
+        final_in_b = true;
+        break;
+      }
+      ia = in;
+      issue(ra, ia);
+      --left;
+      advance();
+      const SpanTile in2 = tile_info();
+      __builtin_amdgcn_sched_barrier(0);
+      one(rb, ib, ia);
+      ib = in2;
+    }
+    if (final_in_b) {
+      compute(rb, ib);
+      ia = ib;
+    } else {
+      compute(ra, ia);
+    }
+    finish(ia);
+  }
+  __syncthreads();
+
+  // ---- join the parts of each cut route over the workgroup's columns: every
+  // thread forms the weights of its head itself, all loads of a route's parts
+  // independent of each other
+  constexpr int NP = 2 * kWaves;
+  const float* s_ml = s_dyn + NP * G * kLdsStride;
+  const int wt0 = sc.begin(min(blk * kWaves, sc.cols));
+  const int wt1 = sc.begin(min(blk * kWaves + kWaves, sc.cols));
+  int part[NP];
+#pragma unroll
+  for (int k = 0; k < NP; ++k) part[k] = uni(s_part[k]);
+  int done = -1;  // a route's parts are in consecutive slots, so each is met once
+#pragma unroll 1
+  for (int i = 0; i < NP; ++i) {
+    const int u = uni(s_part[i]);
+    if (u < 0 || u == done) continue;
+    done = u;
+    const bool whole = s_pre[u] >= wt0 && s_pre[u + 1] <= wt1;
+    const size_t rec = ((size_t)(blk + min(u, sc.of(s_pre[u]) / kWaves)) * H + g) * G;
+    const int r = a.route_list ? as_const(a.route_list)[u] : u;
+#pragma unroll 1
+    for (int e = tid; e < G * (kDim / 4); e += kThreads) {  // four dims of one head
+      const int h = e / (kDim / 4), d = e % (kDim / 4) * 4;
+      float m[NP], M = neg_inf();
+      bool nan = false;
+#pragma unroll
+      for (int k = 0; k < NP; ++k) {
+        m[k] = part[k] == u ? s_ml[(k * G + h) * 2] : neg_inf();
+        nan |= m[k] != m[k];
+        M = fmaxf(M, m[k]);
+      }
+      if (nan) M = qnan();
+      float L = 0.0f;
+      f32x4 O = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int k = 0; k < NP; ++k)
+        if (part[k] == u) {
+          const float wt = m[k] == neg_inf() ? 0.0f : exp2_fast(m[k] - M);
+          L += wt * s_ml[(k * G + h) * 2 + 1];
+          O += wt * *reinterpret_cast<const f32x4*>(s_dyn + (k * G + h) * kLdsStride + d);
+        }
+      if (whole) {
+        const size_t row = (size_t)r * Hq + hq0 + h;
+        *reinterpret_cast<f32x4*>(a.o_part + row * kDim + d) = O / L;
+        if (d == 0) a.lse_part[row] = (M + __log2f(L)) * kLn2;
+      } else {
+        __builtin_nontemporal_store(O, reinterpret_cast<f32x4*>(a.span_o + (rec + h) * kDim + d));
+        if (d == 0) {
+          a.span_ml[(rec + h) * 2] = M;
+          a.span_ml[(rec + h) * 2 + 1] = L;
+        }
+      }
+    }
+  }
+}
+
 // The dispatch order of a split launch of several rounds.  The hardware
 // deals the workgroups of a launch in order over the XCDs and, within an
 // XCD, round-robin over its shader engines, and an XCD stops dealing at a
@@ -1012,7 +1528,7 @@ __global__ __launch_bounds__(1024) void order_kernel(PartialArgs a) {
 }
 
 // The records of one (launch position, query head): k places, `stride`
-// records apart; those in use come first.
+// records apart; those in use come first.  k = 0: the outputs are in place.
 struct Pieces {
   size_t rec0;
   int stride, k;
@@ -1020,6 +1536,10 @@ struct Pieces {
 
 __device__ __forceinline__ Pieces pieces_of(const RecordArgs& a, int u, int h) {
   const int g = h / a.group, hl = h - g * a.group;
+  if (a.span_table) {
+    const int first = a.span_table[2 * u], k = a.span_table[2 * u + 1];
+    return {((size_t)first * a.num_kv_heads + g) * a.group + hl, a.num_kv_heads * a.group, k};
+  }
   return {(((size_t)u * a.num_kv_heads + g) * a.max_chunks) * a.group + hl, a.group, a.max_chunks};
 }
 
@@ -1067,6 +1587,7 @@ __device__ __forceinline__ void piece_sums(const RecordArgs& a, const Pieces& p,
 template <int WAVES>
 __device__ __forceinline__ bool combine_unit(const RecordArgs& a, const Pieces& p, int lane,
                                              int wave, float2 (*s_sum)[64], float2& o, float& lse) {
+  if (p.k == 0) return false;
   const float2* ml = reinterpret_cast<const float2*>(a.ml) + p.rec0;
   auto record = [&](int i) -> float2 {
     return i < p.k ? ml[(size_t)i * p.stride] : make_float2(neg_inf(), 0.0f);
@@ -1457,8 +1978,19 @@ hipError_t launch_partial_kernel(const PartialArgs& a, dim3 grid, hipStream_t st
   return hipGetLastError();
 }
 
+template <bool FP8>
+hipError_t launch_span_kernel(const PartialArgs& a, hipStream_t stream) {
+  const dim3 grid((unsigned)(a.span_cols / kWaves * a.num_kv_heads));
+  const size_t lds = span_lds_bytes(a.group, a.num_units_routes);
+  if (a.head_major)
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(span_kernel<FP8, true>), grid, dim3(kThreads), lds, stream, a);
+  else
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(span_kernel<FP8, false>), grid, dim3(kThreads), lds, stream, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_combine(const RecordArgs& rec, int num_launch, hipStream_t stream) {
-  if (rec.max_chunks > kChunksOneWave)
+  if (rec.places > kChunksOneWave)
     hipLaunchKernelGGL(combine_kernel<4>, dim3(rec.num_q_heads, num_launch), dim3(kThreads), 0,
                        stream, rec);
   else
@@ -1517,6 +2049,11 @@ hipError_t launch_append(const AppendArgs& a, bool fp8, hipStream_t stream) {
 hipError_t launch_partial(const PartialArgs& a, bool fp8, hipStream_t stream) {
   if (a.num_units_routes == 0) return hipSuccess;
   const RecordArgs rec = records_of(a);
+  if (a.span_cols > 0) {
+    const hipError_t es = fp8 ? launch_span_kernel<true>(a, stream) : launch_span_kernel<false>(a, stream);
+    if (es != hipSuccess || a.merge_combines) return es;
+    return launch_combine(rec, a.num_units_routes, stream);
+  }
   if (!fp8 && a.units_per_wg == 2)
     return launch_partial_kernel<false, 2>(a, dim3(1, a.num_kv_heads, (a.num_units_routes + 1) / 2),
                                            stream);
@@ -1549,7 +2086,7 @@ hipError_t launch_merge(const MergeArgs& a, hipStream_t stream) {
   if (a.num_seqs == 0 || a.num_q_heads == 0) return hipSuccess;
   const dim3 grid(a.num_q_heads + (a.tail_route ? 1 : 0), a.num_seqs);
   const int rows = a.num_routes / a.num_seqs;  // mean rows per sequence
-  if (a.rec.ml && (rows > 0 ? rows : 1) * a.rec.max_chunks <= kRecordsOneWave)
+  if (a.rec.ml && (rows > 0 ? rows : 1) * a.rec.places <= kRecordsOneWave)
     hipLaunchKernelGGL(HIP_KERNEL_NAME(merge_kernel<1, true>), grid, dim3(64), 0, stream, a);
   else if (a.rec.ml)
     hipLaunchKernelGGL(HIP_KERNEL_NAME(merge_kernel<4, true>), grid, dim3(256), 0, stream, a);

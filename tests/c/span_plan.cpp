@@ -1,0 +1,83 @@
+// Host check of the span planner (kf_api.cpp built against the HIP test
+// double): over random launches on devices of 8 to 1024 compute units, a span
+// plan's workspace fits both a workspace sized by the query for any table at
+// least as large and the library's scratch array, its regions do not meet,
+// and the record places of the cut routes are distinct and inside the plan.
+#include <stdio.h>
+
+#include <algorithm>
+#include <random>
+#include <vector>
+
+#include "kf.h"
+#include "kf_internal.h"
+
+static int g_cus = 256;
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = g_cus; return hipSuccess; }
+namespace kf {
+hipError_t launch_append(const AppendArgs&, bool, hipStream_t) { return hipSuccess; }
+hipError_t launch_partial(const PartialArgs&, bool, hipStream_t) { return hipSuccess; }
+hipError_t launch_merge(const MergeArgs&, hipStream_t) { return hipSuccess; }
+hipError_t launch_gather(const PartialArgs&, bool, int, int, void*, void*, hipStream_t) { return hipSuccess; }
+hipError_t scratch_address(void** out) { *out = nullptr; return hipSuccess; }
+}  // namespace kf
+
+static std::mt19937 rng(7);
+static int64_t rnd(int64_t lo, int64_t hi) { return std::uniform_int_distribution<int64_t>(lo, hi)(rng); }
+
+#define CHECK(c)                                                   \
+  do {                                                             \
+    if (!(c)) {                                                    \
+      printf("line %d: %s (R=%d H=%d G=%d P=%d fp8=%d wg=%d)\n", __LINE__, #c, R, H, G, maxp, fp8, p.wg_cols); \
+      return 1;                                                    \
+    }                                                              \
+  } while (0)
+
+int main(int argc, char** argv) {
+  g_cus = argc > 1 ? atoi(argv[1]) : 256;  // one device per process: the count is cached
+  int spans = 0;
+  for (int it = 0; it < 4000; ++it) {
+    const int hs[] = {1, 2, 4, 8, 16, 32, 40, 600};
+    const int R = (int)(rnd(0, 3) ? rnd(1, 300) : rnd(1, 1200)), H = hs[rnd(0, 7)], G = (int)rnd(1, 16);
+    const int maxp = (int)(rnd(0, 3) ? rnd(1, 600) : rnd(1, 9000));
+    const bool fp8 = rnd(0, 1), list = !rnd(0, 9);
+    kf_shape s{1, G * H, H, KF_HEAD_DIM, KF_PAGE_SIZE, fp8 ? KF_KV_FP8_E4M3 : KF_KV_BF16, 10,
+               (int)rnd(1, (int64_t)R * maxp), 0.1f, 0};
+    const int64_t slots = 2 * (int64_t)g_cus;
+    const kf::ChunkPlan c = kf::plan_chunks(R, H, maxp, kf::ragged_table(s.num_page_ids, R, maxp), fp8, list);
+    const kf::SpanPlan p = kf::plan_span(R, H, G, maxp, s.num_page_ids, fp8, list, c, slots);
+    if (!p.wg_cols) continue;
+    ++spans;
+    CHECK(!list && R <= kf::kSpanRoutes && kf::span_lds_bytes(G, R) <= kf::kSpanLds);
+    CHECK((int64_t)p.wg_cols * H <= std::max<int64_t>(slots, H));
+    CHECK(p.total <= KF_SCRATCH_BYTES);
+    CHECK(p.total <= kf_partial_attn_workspace_bytes(&s, R, maxp));
+    CHECK(p.total <= kf_partial_attn_workspace_bytes(&s, R + (int)rnd(0, 50), maxp));
+    const int64_t places = p.wg_cols + std::min(p.wg_cols, R), recs = places * H * G;
+    CHECK((int64_t)p.ml_off >= R * 8 && (int64_t)(p.o_off - p.ml_off) >= recs * 8 &&
+          (int64_t)(p.total - p.o_off) >= recs * kf::kDim * 4);
+    // the kernel's columns over random route lengths
+    std::vector<int> tiles(R);
+    int64_t T = 0;
+    for (int& t : tiles) T += t = rnd(0, 4) ? (int)rnd(0, maxp) : 0;
+    const int64_t cols = std::max<int64_t>(1, std::min<int64_t>(p.wg_cols * kf::kWaves, T));
+    if (!T) continue;
+    const int64_t q = T / cols, rem = T % cols, edge = rem * (q + 1);
+    auto of = [&](int64_t t) { return t < edge ? t / (q + 1) : rem + (t - edge) / q; };
+    std::vector<char> used(places, 0);
+    int64_t pre = 0;
+    for (int u = 0; u < R; pre += tiles[u], ++u) {
+      if (!tiles[u]) continue;
+      const int64_t c0 = of(pre) / kf::kWaves, c1 = of(pre + tiles[u] - 1) / kf::kWaves;
+      for (int64_t w = c0; c1 > c0 && w <= c1; ++w) {
+        const int64_t at = w + std::min<int64_t>(u, c0);
+        CHECK(at < places && !used[at]);
+        used[at] = 1;
+      }
+    }
+  }
+  printf("span_plan ok: %d span launches\n", spans);
+  return spans > 100 ? 0 : 1;
+}

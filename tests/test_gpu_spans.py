@@ -1,0 +1,106 @@
+"""Span launches: a ragged batch's tiles, route after route, cut into equal
+wave columns.  Each case is checked against the oracle and against the same
+batch launched over an identity route list, which keeps the chunk plan, and
+as a fused step bit for bit against its three calls and against the step that
+uses the library's scratch array."""
+import numpy as np
+import pytest
+
+from kf_testlib import compare_all, host, run_gpu, run_oracle
+from kf_workloads import make_instance, workload
+
+pytestmark = pytest.mark.gpu
+
+# (q heads, KV heads, fp8, lengths, route length); lengths reach two tiles per
+# wave: pages * KV heads >= 8192 (bf16, 2-page tiles) or 16384 (fp8, 4-page)
+_RAGGED = [
+    # ends at, before and past pages and tiles, one-token and empty sequences
+    (32, 8, False, [1, 16, 17, 31, 32, 33, 48, 0, 2048, 5000, 7777, 1, 0, 1500], 65536),
+    # one long route cut over most columns beside short ones
+    (8, 2, False, [65000, 5, 900, 1, 33], 65536),
+    # more routes than workgroup columns (record places by column), 16 KV heads
+    (16, 16, False, [int(x) for x in np.random.default_rng(3).integers(1, 700, 60)], 65536),
+    # 16 query heads per KV head, several routes per sequence
+    (64, 4, False, [9000, 17000, 2100, 6001, 40], 4096),
+    # one KV head and a group of 3
+    (3, 1, False, [100000, 50000, 1000, 7], 65536),
+    # fp8, groups of 8 and 1, tiles of 4 pages
+    (64, 8, True, [3, 16, 4096, 64, 65, 12000, 63, 0, 18001, 33], 65536),
+    (4, 4, True, [40000, 29000, 128, 8000, 1], 65536),
+]
+
+
+def _instance(case, steps, seed=5):
+    hq, hkv, fp8, lens, part = case
+    wl = workload("llama8b_32k", num_seqs=len(lens), num_q_heads=hq, num_kv_heads=hkv,
+                  part_tokens=part, kv_dtype="fp8" if fp8 else "bf16", permuted=True)
+    return make_instance(wl, seed=seed, steps=steps, seq_lens=lens)
+
+
+def _is_span(inst):
+    """The launch rule: a ragged table with two tiles per wave."""
+    n, r, most = len(inst.page_ids), len(inst.routes), inst.max_pages_per_route
+    tile = 4 if inst.k_scale is not None else 2
+    return n * 10 < r * most * 9 and n * inst.wl.num_kv_heads >= 2 * tile * 2048 and r <= 1024 and \
+        (most > 32 or inst.wl.group <= 8)
+
+
+@pytest.mark.parametrize("case", _RAGGED, ids=lambda c: f"{c[0]}q{c[1]}kv{'fp8' if c[2] else ''}")
+def test_span_launch_matches_oracle_and_chunk_plan(gpu, case):
+    import torch
+    from paper_2606_29207_amd import kf
+    inst = _instance(case, steps=2)
+    assert _is_span(inst)
+    o = run_oracle(inst, 2)
+    st = run_gpu(inst, 2)
+    g = host(st)
+    compare_all(g, o)
+    fused = host(run_gpu(inst, 2, fused=True))
+    for k in g:
+        if g[k] is None:
+            continue
+        assert np.array_equal(np.asarray(g[k]), np.asarray(fused[k]), equal_nan=True), k
+    # the chunk plan on the same state: other sums, the same values to float32
+    # rounding (a few hundred 2^-24 steps over sums of up to 65536 terms)
+    o_part, lse_part = st.o_part.clone(), st.lse_part.clone()
+    ident = torch.arange(len(inst.routes), dtype=torch.int32, device=st.device)
+    kf.partial_attn(st.shape, st.q, st.k_pool, st.v_pool, st.routes, st.max_pages_per_route,
+                    st.page_ids, st.o_part, st.lse_part, st.workspace, st.err_flags,
+                    k_scale=st.k_scale, v_scale=st.v_scale, route_list=ident)
+    torch.cuda.synchronize()
+    err = (o_part - st.o_part).norm() / st.o_part.norm()
+    assert err <= 2e-5, float(err)
+    both = torch.isfinite(lse_part)
+    assert torch.equal(both, torch.isfinite(st.lse_part))
+    assert (lse_part[both] - st.lse_part[both]).abs().max() <= 2e-5
+
+
+def test_span_step_without_a_workspace_is_the_same(gpu):
+    import torch
+    from paper_2606_29207_amd.step import DecodeState
+    inst = _instance(_RAGGED[0], steps=1, seed=6)
+    a, b = DecodeState.from_instance(inst), DecodeState.from_instance(inst)
+    tok = a.upload_new_tokens(*inst.new_tokens(0))
+    a.step_fused(*tok)
+    b.step_no_alloc(*tok)
+    torch.cuda.synchronize()
+    for n in ("o_part", "lse_part", "out", "lse", "routes", "k_pool", "v_pool"):
+        x, y = getattr(a, n), getattr(b, n)   # bits: unused slots are NaN
+        bits = torch.int16 if x.element_size() == 2 else torch.int32
+        assert torch.equal(x.view(bits), y.view(bits)), n
+
+
+def test_span_launch_with_bad_rows_and_pages(gpu):
+    """A row of a wrong sequence, one that needs more pages than the launch
+    allows, a page id outside the pool in the middle of a cut route, an
+    inverted CSR row: NaN and flags as the oracle has them, other rows whole."""
+    inst = _instance(_RAGGED[0], steps=1, seed=7)
+    assert _is_span(inst)
+    inst.routes[2, 0] = 99                     # no such sequence
+    inst.routes[4, 3] = inst.routes[4, 2] - 3  # ends before it begins
+    inst.page_ids[inst.routes[10, 4] + 150] = inst.num_pages + 5
+    inst.seq_route_begin[9] = inst.seq_route_begin[8] - 1
+    o = run_oracle(inst, 1)
+    for fused in (False, True):
+        g = host(run_gpu(inst, 1, fused=fused))
+        compare_all(g, o)
