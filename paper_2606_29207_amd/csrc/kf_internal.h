@@ -20,6 +20,7 @@ constexpr int kMinRangePagesMany = 256;  // ... in bf16 launches of at least a r
 constexpr int kMaxPagesTwoUnit = 2048;  // longest units run two per workgroup (bf16, unsplit)
 constexpr int kMaxLaunchRoutes = 65535;  // routes per launch and KV heads: grid dimension limits
 constexpr int kChunksOneWave = 8;        // ranges per unit up to which one wave combines a head
+constexpr int64_t kEarlyRecordHeads = 2048;  // most (route, head) pairs whose records load early
 constexpr int kRecordsOneWave = 8;       // mean records per (sequence, head) up to which one wave merges them
 constexpr int kLdsRows = 16;             // rows per sequence that a combining merge keeps in LDS
 constexpr int kLdsStride = kDim + 4;     // padded row of an output buffer in LDS

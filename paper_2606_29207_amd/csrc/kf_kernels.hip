@@ -2,8 +2,9 @@
 // (KernelFlume, arXiv 2606.29207, Section 3.2 steps 3-4, Section 5.1):
 //   append_kernel   -- tail append of the step's K/V token
 //   partial_kernel  -- local attention over token-range routes -> (o, lse)
+//   span_kernel     -- the same for ragged batches, cut into equal wave columns
 //   order_kernel    -- dispatch order of a split launch of several rounds
-//   combine_kernel  -- in-range reduction of a split unit's ranges
+//   combine_kernel  -- reduction of the records of split units and spans
 //   merge_kernel    -- log-sum-exp merge of the partials of each sequence
 //
 // partial_kernel is HBM-bound (4 flop per KV byte at 4 query heads per KV
@@ -33,8 +34,8 @@
 //     once at the end; the four waves are combined through LDS.
 // Workgroups never exchange data with each other inside a kernel: when a
 // unit is chunked, the chunk partials go to the workspace and combine_kernel
-// (the next launch on the stream) merges them in chunk order, so results are
-// deterministic.
+// or a fused step's merge_kernel (the next launch on the stream) sums them in
+// a fixed order, so results are deterministic.
 #include <atomic>
 #include <mutex>
 #include <type_traits>
@@ -1543,38 +1544,46 @@ __device__ __forceinline__ Pieces pieces_of(const RecordArgs& a, int u, int h) {
   return {(((size_t)u * a.num_kv_heads + g) * a.max_chunks) * a.group + hl, a.group, a.max_chunks};
 }
 
-// Weighted output sums of up to 64 records (record base + i: weight wi in lane
-// off + i, bit i of `used` set if it holds anything), dims 2*lane and 2*lane + 1, added to four subsets of
-// records (subset s: s, s + 4, ...), each in record order.  WAVES = 4: this
-// wave's subset only; WAVES = 1: all four.  Eight records' loads in flight.
+// The outputs (dims 2*lane and 2*lane + 1) of eight records of a block from
+// `base` on, record j first: WAVES = 1 the next eight, WAVES = 4 every fourth,
+// v[q][s] that of record j + 4 * q + s.  Places from cnt on repeat the last
+// (branches round the few loads saved made chat batches 1.5% slower).
 template <int WAVES>
-__device__ __forceinline__ void piece_sums(const RecordArgs& a, const Pieces& p, int base,
-                                           uint64_t used, float wi, int off, int lane, int wave,
-                                           float2 (&acc)[4 / WAVES]) {
-  constexpr int NS = 4 / WAVES, UN = 8 / NS;
-  // places not in use (and ranges whose every score is -inf) add nothing
-  const int cnt = used ? 64 - __builtin_clzll(used) : 0;
+__device__ __forceinline__ void load_pieces(const RecordArgs& a, const Pieces& p, int base, int j,
+                                            int cnt, int lane, float2 (&v)[2 * WAVES][4 / WAVES]) {
   const float2* o = reinterpret_cast<const float2*>(a.o) + lane;
-  for (int j = WAVES == 1 ? 0 : wave; j < cnt; j += 4 * UN) {
-    float2 v[UN][NS];
-    float wt[UN][NS];
+#pragma unroll
+  for (int q = 0; q < 2 * WAVES; ++q)
+#pragma unroll
+    for (int s = 0; s < 4 / WAVES; ++s)
+      v[q][s] = o[(p.rec0 + (size_t)(base + min(j + 4 * q + s, cnt - 1)) * p.stride) * (kDim / 2)];
+}
+
+// Weighted output sums of up to 64 records (record base + i: weight in lane i
+// of wi, bit i of `used` set if it holds anything) added to four subsets of
+// records (subset s: s, s + 4, ...), each in record order.  WAVES = 4: this
+// wave's subset only; WAVES = 1: all four.  Eight records' loads in flight;
+// LOADED: v holds the first eight already.
+template <int WAVES, bool LOADED>
+__device__ __forceinline__ void piece_sums(const RecordArgs& a, const Pieces& p, int base,
+                                           uint64_t used, float wi, int lane, int wave,
+                                           float2 (&v)[2 * WAVES][4 / WAVES],
+                                           float2 (&acc)[4 / WAVES]) {
+  constexpr int NS = 4 / WAVES, UN = 2 * WAVES;
+  // places not in use (and ranges whose every score is -inf) add nothing
+  const int cnt = used ? 64 - __builtin_clzll(used) : 0, j0 = WAVES == 1 ? 0 : wave;
+  for (int j = j0; j < cnt; j += 4 * UN) {
+    if (!LOADED || j != j0) load_pieces<WAVES>(a, p, base, j, cnt, lane, v);
 #pragma unroll
     for (int q = 0; q < UN; ++q)
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         const int jj = min(j + 4 * q + s, cnt - 1);
         const bool in = j + 4 * q + s < cnt && ((used >> jj) & 1);
-        const float w = read_lane(wi, off + jj);
-        wt[q][s] = in ? w : 0.0f;
-        v[q][s] = o[(p.rec0 + (size_t)(base + jj) * p.stride) * (kDim / 2)];
-        if (!in) v[q][s] = make_float2(0.0f, 0.0f);
-      }
-#pragma unroll
-    for (int q = 0; q < UN; ++q)
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        acc[s].x += wt[q][s] * v[q][s].x;
-        acc[s].y += wt[q][s] * v[q][s].y;
+        const float wj = read_lane(wi, jj), w = in ? wj : 0.0f;
+        // explicit FMAs: the same bits from every instantiation
+        acc[s].x = __builtin_fmaf(w, in ? v[q][s].x : 0.0f, acc[s].x);
+        acc[s].y = __builtin_fmaf(w, in ? v[q][s].y : 0.0f, acc[s].y);
       }
   }
 }
@@ -1582,9 +1591,10 @@ __device__ __forceinline__ void piece_sums(const RecordArgs& a, const Pieces& p,
 // Reduce the records of one (launch position, query head) to the normalised
 // output (the lane's dims) and lse; false: the outputs are already in place.
 // WAVES = 4: called by the 256 threads of a workgroup, and the result is wave
-// 0's; WAVES = 1: by one wave.  The same bits either way: every wave forms
+// 0's; WAVES = 1: by one wave.  EARLY: the first outputs' loads go out beside
+// the (max, sum) loads and not after the weights.  The same bits either way: every wave forms
 // the maximum and the sum alike, the outputs add up as ((S0 + S1) + S2) + S3.
-template <int WAVES>
+template <int WAVES, bool EARLY = false>
 __device__ __forceinline__ bool combine_unit(const RecordArgs& a, const Pieces& p, int lane,
                                              int wave, float2 (*s_sum)[64], float2& o, float& lse) {
   if (p.k == 0) return false;
@@ -1593,6 +1603,9 @@ __device__ __forceinline__ bool combine_unit(const RecordArgs& a, const Pieces& 
     return i < p.k ? ml[(size_t)i * p.stride] : make_float2(neg_inf(), 0.0f);
   };
   const float2 first = record(lane);  // all of them, with up to 64 places
+  float2 v[2 * WAVES][4 / WAVES];
+  if constexpr (EARLY)
+    load_pieces<WAVES>(a, p, 0, WAVES == 1 ? 0 : wave, min(p.k, 64), lane, v);
   if (__shfl(first.y, 0) == -1.0f) return false;
   float M = first.x;
   for (int i = lane + 64; i < p.k; i += 64) M = fmaxf(M, record(i).x);
@@ -1603,12 +1616,12 @@ __device__ __forceinline__ bool combine_unit(const RecordArgs& a, const Pieces& 
   float2 acc[4 / WAVES];
 #pragma unroll
   for (int s = 0; s < 4 / WAVES; ++s) acc[s] = make_float2(0.0f, 0.0f);
-  piece_sums<WAVES>(a, p, 0, __ballot(first.x != neg_inf()), w, 0, lane, wave, acc);
+  piece_sums<WAVES, EARLY>(a, p, 0, __ballot(first.x != neg_inf()), w, lane, wave, v, acc);
   for (int base = 64; base < p.k; base += 64) {
     const float2 r = record(base + lane);
     w = weight(r.x);
-    L += r.x == neg_inf() ? 0.0f : w * r.y;
-    piece_sums<WAVES>(a, p, base, __ballot(r.x != neg_inf()), w, 0, lane, wave, acc);
+    L = r.x == neg_inf() ? L : __builtin_fmaf(w, r.y, L);
+    piece_sums<WAVES, false>(a, p, base, __ballot(r.x != neg_inf()), w, lane, wave, v, acc);
   }
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) L += __shfl_xor(L, m);
@@ -1653,7 +1666,7 @@ __device__ __forceinline__ void store_row(const RecordArgs& a, int r, int h, int
 // Combine the records of each (launch position, query head) whose outputs are
 // not in place yet: one wave each (four heads per workgroup), or, with many
 // records, the four waves of a workgroup.
-template <int WAVES>
+template <int WAVES, bool EARLY>
 __global__ __launch_bounds__(kThreads) void combine_kernel(RecordArgs a) {
   __shared__ float2 s_sum[4][64];
   const int u = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1663,7 +1676,7 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(RecordArgs a) {
   if (r < 0 || r >= a.num_routes) return;  // flagged by partial_kernel
   float2 o;
   float lse;
-  if (combine_unit<WAVES>(a, pieces_of(a, u, h), lane, wave, s_sum, o, lse) &&
+  if (combine_unit<WAVES, EARLY>(a, pieces_of(a, u, h), lane, wave, s_sum, o, lse) &&
       (WAVES == 1 || wave == 0))
     store_row(a, r, h, lane, o, lse);
 }
@@ -1721,7 +1734,10 @@ __device__ __forceinline__ int tail_append_status(const MergeArgs& a, int b, int
 // Bound by reading the rows once more rows arrive than one wave's loads in
 // flight cover: 128 rows per sequence (32 sequences, 32 heads, 68 MB) took
 // 16.1 us with one wave of four loads, 12.5 us with four waves of eight (16
-// each: 13.2); below eight rows a sequence one wave is enough.
+// each: 13.2); below eight rows a sequence one wave is enough.  A wave's first
+// eight rows are loaded beside their lse, not after the weights, and only rows
+// that there are: 128 rows 12.5 -> 12.3 us, 32 to 100
+// sequences of 3 or 4 rows 4.2 -> 3.75.
 //
 // Sequence b's rows r0 .. r0 + n - 1 of query head h merged by WAVES waves;
 // lane holds dims 2*lane, 2*lane+1.  Rows are summed in four subsets (subset
@@ -1736,9 +1752,26 @@ __device__ __forceinline__ void merge_rows(const MergeArgs& a, int b, int h, int
   const float* lse = a.lse_part + (size_t)r0 * Hq + h;
   float2* out = reinterpret_cast<float2*>(a.out + ((size_t)b * Hq + h) * kDim) + lane;
   float* lse_out = a.lse_out + (size_t)b * Hq + h;
-  float M = neg_inf();
-  bool nan_seen = false;
-  for (int i = WAVES == 1 ? lane : 64 * wave + lane; i < n; i += 64 * WAVES) {
+  constexpr int BLOCK = 64 * WAVES;  // rows whose weights one block of lanes holds
+  const size_t rs = (size_t)Hq * kDim / 2;  // float2 elements from one row to the next
+  const float2* o = reinterpret_cast<const float2*>(a.o_part + ((size_t)r0 * Hq + h) * kDim) + lane;
+  // the lane's row of a block (one wave: base + lane), and the wave's first row
+  const int mine = WAVES == 1 ? lane : 4 * lane + wave, j0 = WAVES == 1 ? 0 : wave;
+  const float first = mine < n ? lse[(size_t)mine * Hq] : neg_inf();
+  float2 v[UN][NS];
+  auto load = [&](int base, int j) {  // rows that there are: n and j are uniform
+#pragma unroll
+    for (int q = 0; q < UN; ++q)
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        v[q][s] = make_float2(0.0f, 0.0f);
+        if (base + j + 4 * q + s < n) v[q][s] = o[(size_t)(base + j + 4 * q + s) * rs];
+      }
+  };
+  load(0, j0);
+  float M = first;
+  bool nan_seen = first != first;
+  for (int i = mine + BLOCK; i < n; i += BLOCK) {
     const float l = lse[(size_t)i * Hq];
     nan_seen |= l != l;
     M = fmaxf(M, l);
@@ -1768,35 +1801,23 @@ __device__ __forceinline__ void merge_rows(const MergeArgs& a, int b, int h, int
   float3 acc[NS];
 #pragma unroll
   for (int s = 0; s < NS; ++s) acc[s] = make_float3(0.0f, 0.0f, 0.0f);
-  const size_t rs = (size_t)Hq * kDim / 2;  // float2 elements from one row to the next
-  const float2* o = reinterpret_cast<const float2*>(a.o_part + ((size_t)r0 * Hq + h) * kDim) + lane;
-  constexpr int BLOCK = 64 * WAVES;  // rows whose weights one block of lanes holds
   for (int base = 0; base < n; base += BLOCK) {
-    // one wave: row base + lane; four: row base + 4 * lane + wave
-    const int i = WAVES == 1 ? base + lane : base + 4 * lane + wave;
-    const float wl = i < n ? exp2_fast((lse[(size_t)i * Hq] - M) * kLog2e) : 0.0f;
+    const int i = base + mine;
+    const float l = base == 0 ? first : i < n ? lse[(size_t)i * Hq] : neg_inf();
+    const float wl = i < n ? exp2_fast((l - M) * kLog2e) : 0.0f;
     const int cnt = min(BLOCK, n - base);
-    for (int j = WAVES == 1 ? 0 : wave; j < cnt; j += 4 * UN) {
-      float2 v[UN][NS];
-      float wr[UN][NS];
+    for (int j = j0; j < cnt; j += 4 * UN) {
+      if (base + j > j0) load(base, j);
 #pragma unroll
       for (int q = 0; q < UN; ++q)
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-          const int jj = j + 4 * q + s;
-          const int jc = min(jj, cnt - 1);
+          const int jj = j + 4 * q + s, jc = min(jj, cnt - 1);
           const float wj = read_lane(wl, WAVES == 1 ? jc : jc >> 2);
-          wr[q][s] = jj < cnt ? wj : 0.0f;
-          v[q][s] = o[(size_t)(base + jc) * rs];
-          if (jj >= cnt) v[q][s] = make_float2(0.0f, 0.0f);
-        }
-#pragma unroll
-      for (int q = 0; q < UN; ++q)
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          acc[s].x += wr[q][s] * v[q][s].x;
-          acc[s].y += wr[q][s] * v[q][s].y;
-          acc[s].z += wr[q][s];
+          const float wr = jj < cnt ? wj : 0.0f;
+          acc[s].x = __builtin_fmaf(wr, v[q][s].x, acc[s].x);
+          acc[s].y = __builtin_fmaf(wr, v[q][s].y, acc[s].y);
+          acc[s].z += wr;
         }
     }
   }
@@ -1854,8 +1875,8 @@ __device__ __forceinline__ void merge_lds_rows(const MergeArgs& a, int b, int h,
       if (j + s < n) {
         const float w = read_lane(wl, j + s);
         const float2 v = s_row[j + s][lane];
-        acc[s].x += w * v.x;
-        acc[s].y += w * v.y;
+        acc[s].x = __builtin_fmaf(w, v.x, acc[s].x);
+        acc[s].y = __builtin_fmaf(w, v.y, acc[s].y);
         acc[s].z += w;
       }
   float3 t = acc[0];
@@ -1989,13 +2010,14 @@ hipError_t launch_span_kernel(const PartialArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+template <bool EARLY>
 hipError_t launch_combine(const RecordArgs& rec, int num_launch, hipStream_t stream) {
   if (rec.places > kChunksOneWave)
-    hipLaunchKernelGGL(combine_kernel<4>, dim3(rec.num_q_heads, num_launch), dim3(kThreads), 0,
-                       stream, rec);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(combine_kernel<4, EARLY>),
+                       dim3(rec.num_q_heads, num_launch), dim3(kThreads), 0, stream, rec);
   else
-    hipLaunchKernelGGL(combine_kernel<1>, dim3((rec.num_q_heads + 3) / 4, num_launch),
-                       dim3(kThreads), 0, stream, rec);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(combine_kernel<1, EARLY>),
+                       dim3((rec.num_q_heads + 3) / 4, num_launch), dim3(kThreads), 0, stream, rec);
   return hipGetLastError();
 }
 
@@ -2052,7 +2074,7 @@ hipError_t launch_partial(const PartialArgs& a, bool fp8, hipStream_t stream) {
   if (a.span_cols > 0) {
     const hipError_t es = fp8 ? launch_span_kernel<true>(a, stream) : launch_span_kernel<false>(a, stream);
     if (es != hipSuccess || a.merge_combines) return es;
-    return launch_combine(rec, a.num_units_routes, stream);
+    return launch_combine<false>(rec, a.num_units_routes, stream);
   }
   if (!fp8 && a.units_per_wg == 2)
     return launch_partial_kernel<false, 2>(a, dim3(1, a.num_kv_heads, (a.num_units_routes + 1) / 2),
@@ -2066,7 +2088,14 @@ hipError_t launch_partial(const PartialArgs& a, bool fp8, hipStream_t stream) {
   hipError_t e = fp8 ? launch_partial_kernel<true, 1>(a, grid, stream)
                      : launch_partial_kernel<false, 1>(a, grid, stream);
   if (e != hipSuccess || a.max_chunks == 1 || a.merge_combines) return e;
-  return launch_combine(rec, a.num_units_routes, stream);
+  // Early output loads pay where almost all record places are in use, as in
+  // equal tables, and the launch is small enough for its latency to count
+  // (4096 tokens, 2 KV heads: step 13.9 -> 13.2 us); in a ragged one
+  // the loads of unused places cost more (8 chats: 20.5 -> 20.8 us).
+  if (!a.route_list && (int64_t)a.num_units_routes * a.num_q_heads <= kEarlyRecordHeads &&
+      !ragged_table(a.num_page_ids, a.num_units_routes, a.max_pages_per_route))
+    return launch_combine<true>(rec, a.num_units_routes, stream);
+  return launch_combine<false>(rec, a.num_units_routes, stream);
 }
 
 hipError_t launch_gather(const PartialArgs& a, bool fp8, int route, int max_tokens, void* out_k,
