@@ -104,3 +104,21 @@ def test_span_launch_with_bad_rows_and_pages(gpu):
     for fused in (False, True):
         g = host(run_gpu(inst, 1, fused=fused))
         compare_all(g, o)
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+def test_span_launch_skips_runs_of_empty_routes(gpu, fp8):
+    """More than a wave of empty routes before, between and behind those with
+    tokens, as in a table of fixed size: waves step over them to their next
+    tile and to their next token.  Two of the empty ones are tails and take a
+    token (the first and the last row of a run), one is a bad row's."""
+    lens = [0] * 70 + [14000 if fp8 else 7000, 17] + [0] * 130 + [33, 18000 if fp8 else 8500] + [0] * 66
+    inst = _instance((64, 8, fp8, lens, 65536) if fp8 else (32, 8, fp8, lens, 65536), steps=2, seed=8)
+    assert len(inst.routes) == len(lens) and _is_span(inst)
+    tail = np.where(np.asarray(lens) > 0, inst.tail_route, -1)
+    for b in (0, 201, 205, 269):
+        tail[b] = inst.tail_route[b]
+    inst.routes[205, 4] = len(inst.page_ids) + 3   # no such page list: bad, takes no token
+    o = run_oracle(inst, 2, tail_route=tail)
+    for fused in (False, True):
+        compare_all(host(run_gpu(inst, 2, tail_route=tail, fused=fused)), o)
