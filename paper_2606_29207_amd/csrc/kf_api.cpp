@@ -271,12 +271,18 @@ SpanPlan plan_span(int32_t num_launch, int32_t num_kv_heads, int32_t group,
   return SpanPlan{};
 }
 
-// The merge of a fused step also combines a split launch's records unless a
-// sequence may hold so many routes that its one workgroup per head would
-// take them one after another for too long.  Merged: chat batches (8
-// sequences, 9 ranges) 24.2 -> 19.9 us per step, 64 fp8 sequences 62.2 -> 55.4.
+// The merge of a fused step also combines a split launch's records in small
+// tables where nearly every sequence has one route: 8 chats 24.2 us per step
+// against 26.3 with a combine launch, 64 fp8 sequences 68.6 against 71.7; at
+// 192 sequences the difference is 0.5%.  One workgroup per head takes all rows
+// of a sequence, so with more rows than sequences the combine launch, which
+// spreads them, is as fast (63 rows of 16 sequences 52.9 and 52.8 us) or faster,
+// the more so the more of them one sequence holds (92 rows of 24, 40 of one:
+// 83.9 and 72.1 us; 44 of 8, 37 of one: 37.6 and 31.2; 200 of one, 199 empty
+// sequences beside it: 191.2 and 160.9).  With this bound a sequence beside
+// others of one route or more has at most kLdsRows.
 bool merge_combines(int32_t num_routes, int32_t num_seqs) {
-  return num_routes <= 4 * (int64_t)num_seqs + 12;
+  return num_routes <= kCombineRows && num_routes < (int64_t)num_seqs + kLdsRows;
 }
 
 bool ordered_dispatch(const ChunkPlan& plan, int32_t num_launch, int32_t num_kv_heads,

@@ -1670,6 +1670,100 @@ __device__ __forceinline__ void store_row(const RecordArgs& a, int r, int h, int
   if (lane == 0) a.lse_part[row] = lse;
 }
 
+// Combine up to 64 rows of one query head by one wave: lane i holds launch
+// position u (-1: none).  sink(i, o, lse) takes each row that has records;
+// returns their lanes (the outputs of the others are in place).  Bound by the
+// chain table, (max, sum), outputs of a row, so four rows walk it together,
+// 16 lanes holding the (max, sum) pairs of each; rows of more records go one
+// by one.  combine_unit's sums in combine_unit's order: the same bits.
+template <class Sink>
+__device__ __forceinline__ uint64_t combine_rows(const RecordArgs& a, int u, int h, int lane,
+                                                 Sink&& sink) {
+  constexpr int R = 4, K = 64 / R;
+  Pieces p{0, 0, 0};
+  if (u >= 0) {
+    p = pieces_of(a, u, h);
+    if (p.k > 0 && a.ml[p.rec0 * 2 + 1] == -1.0f) p.k = 0;  // in place (mark_whole)
+  }
+  const int stride = a.span_table ? a.num_kv_heads * a.group : a.group;
+  const int rec0 = (int)p.rec0;  // a workspace of 2^31 records would be 1 TB
+  const uint64_t all = __ballot(p.k > 0), many = __ballot(p.k > K);
+  const float2* ml = reinterpret_cast<const float2*>(a.ml);
+  const float2* out = reinterpret_cast<const float2*>(a.o) + lane;
+  for (uint64_t left = all & ~many; left;) {
+    int row[R], rec[R], k[R], cnt = 0, kmax = 0;
+#pragma unroll
+    for (int s = 0; s < R; ++s) {  // places past the last row repeat the first
+      row[s] = left ? __builtin_ctzll(left) : row[0];
+      cnt += left != 0;
+      left &= left - 1;
+      rec[s] = __builtin_amdgcn_readlane(rec0, row[s]);
+      k[s] = __builtin_amdgcn_readlane(p.k, row[s]);
+      kmax = max(kmax, k[s]);
+    }
+    const int ms = lane / K, mi = lane % K;
+    const bool in = mi < pick4(k[0], k[1], k[2], k[3], ms);
+    const float2 r = in ? ml[pick4(rec[0], rec[1], rec[2], rec[3], ms) + (size_t)mi * stride]
+                        : make_float2(neg_inf(), 0.0f);
+    float2 v[R][4], acc[R][4];
+    auto load = [&](int j) {
+#pragma unroll
+      for (int s = 0; s < R; ++s)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          v[s][q] = out[(rec[s] + (size_t)min(j + q, k[s] - 1) * stride) * (kDim / 2)];
+    };
+    load(0);
+    float M = r.x;
+#pragma unroll
+    for (int m = K / 2; m >= 1; m >>= 1) M = fmaxf(M, __shfl_xor(M, m));
+    const float w = r.x == neg_inf() ? 0.0f : exp2_fast(r.x - M);
+    float L = r.x == neg_inf() ? 0.0f : w * r.y;
+#pragma unroll
+    for (int m = K / 2; m >= 1; m >>= 1) L += __shfl_xor(L, m);
+    const uint64_t used = __ballot(r.x != neg_inf());
+#pragma unroll
+    for (int s = 0; s < R; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[s][q] = make_float2(0.0f, 0.0f);
+    for (int j = 0; j < kmax; j += 4) {
+      if (j > 0) load(j);
+#pragma unroll
+      for (int s = 0; s < R; ++s)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int i = K * s + j + q;
+          const bool has = (used >> i) & 1;
+          const float wj = has ? read_lane(w, i) : 0.0f;
+          acc[s][q].x = __builtin_fmaf(wj, has ? v[s][q].x : 0.0f, acc[s][q].x);
+          acc[s][q].y = __builtin_fmaf(wj, has ? v[s][q].y : 0.0f, acc[s][q].y);
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < R; ++s) {
+      if (s >= cnt) break;
+      float2 t = acc[s][0];
+#pragma unroll
+      for (int q = 1; q < 4; ++q) {
+        t.x += acc[s][q].x;
+        t.y += acc[s][q].y;
+      }
+      const float Ls = read_lane(L, K * s), Ms = read_lane(M, K * s);
+      sink(row[s], make_float2(t.x / Ls, t.y / Ls), (Ms + __log2f(Ls)) * kLn2);
+    }
+  }
+  for (uint64_t left = many; left; left &= left - 1) {
+    const int i = __builtin_ctzll(left);
+    float2 o;
+    float lse;
+    combine_unit<1>(a, {(size_t)__builtin_amdgcn_readlane(rec0, i), stride,
+                        __builtin_amdgcn_readlane(p.k, i)},
+                    lane, 0, nullptr, o, lse);
+    sink(i, o, lse);
+  }
+  return all;
+}
+
 // Small and bound by its chain of dependent loads, so the chain is short:
 // every (max, sum) of a head arrives in one load and its weights are read
 // across lanes, no route row is read (mark_whole), eight records' outputs are
@@ -1919,28 +2013,26 @@ __device__ __forceinline__ void step_bookkeeping(const MergeArgs& a, int b, int 
       atomicOr(a.err_flags, st >> 8);
   }
   if constexpr (RECORDS) {
-    for (int64_t base = 64 * ((int64_t)b * WAVES + wave); base < a.num_routes;
-         base += 64 * (int64_t)a.num_seqs * WAVES) {
-      const int u = (int)base + lane;
-      bool orphan = false;
-      if (u < a.num_routes) {
-        const int seq = a.routes[u].seq;
-        orphan = seq < 0 || seq >= a.num_seqs;
-        if (!orphan) {
-          const int r0 = a.seq_route_begin[seq], r1 = a.seq_route_begin[seq + 1];
-          orphan = r0 < 0 || r1 > a.num_routes || u < r0 || u >= r1;
-        }
-      }
-      for (uint64_t left = __ballot(orphan); left; left &= left - 1) {
-        const int r = (int)base + __builtin_ctzll(left);
-        for (int h = 0; h < a.num_q_heads; ++h) {
-          float2 o;
-          float lse;
-          if (combine_unit<1>(a.rec, pieces_of(a.rec, r, h), lane, wave, nullptr, o, lse))
-            store_row(a.rec, r, h, lane, o, lse);
-        }
+    // every wave takes 64 rows and a share of the heads; there are at least
+    // as many waves as blocks of rows (merge_combines)
+    const int blocks = (a.num_routes + 63) / 64, id = b * WAVES + wave;
+    const int share = a.num_seqs * WAVES / blocks;
+    if (id >= share * blocks) return;
+    const int u = id % blocks * 64 + lane;
+    bool orphan = false;
+    if (u < a.num_routes) {
+      const int seq = a.routes[u].seq;
+      orphan = seq < 0 || seq >= a.num_seqs;
+      if (!orphan) {
+        const int r0 = a.seq_route_begin[seq], r1 = a.seq_route_begin[seq + 1];
+        orphan = r0 < 0 || r1 > a.num_routes || u < r0 || u >= r1;
       }
     }
+    if (__ballot(orphan) == 0) return;
+    for (int h = id / blocks; h < a.num_q_heads; h += share)
+      combine_rows(a.rec, orphan ? u : -1, h, lane, [&](int i, float2 o, float lse) {
+        store_row(a.rec, id % blocks * 64 + i, h, lane, o, lse);
+      });
   }
 }
 
@@ -1975,27 +2067,55 @@ __global__ __launch_bounds__(64 * WAVES) void merge_kernel(MergeArgs a) {
     __shared__ float2 s_rec[WAVES][64];
     __shared__ float s_lse[kLdsRows];
     const int n = r1 - r0;
-    const bool share = WAVES == 4 && n == 1;  // one row: the waves share its records
-    for (int i = share ? 0 : wave; i < n; i += share ? 1 : WAVES) {
-      const size_t row = (size_t)(r0 + i) * Hq + h;
+    if (n == 1) {
+      const Pieces p = pieces_of(a.rec, r0, h);
+      const bool share = WAVES == 4 && p.k > kRecordsOneWave;
+      if (wave != 0 && !share) return;
+      const size_t row = (size_t)r0 * Hq + h;
       // a whole unit's row is in place; its loads go out with the records'
       float2 o = reinterpret_cast<const float2*>(a.o_part)[row * (kDim / 2) + lane];
       float lse = a.lse_part[row];
-      const Pieces p = pieces_of(a.rec, r0 + i, h);
       const bool got = WAVES == 4 && share
                            ? combine_unit<WAVES>(a.rec, p, lane, wave, s_rec, o, lse)
                            : combine_unit<1>(a.rec, p, lane, wave, s_rec, o, lse);
-      if (share && wave != 0) continue;
-      if (got) store_row(a.rec, r0 + i, h, lane, o, lse);
-      if (n <= kLdsRows) {
-        s_row[i][lane] = o;
-        if (lane == 0) s_lse[i] = lse;
-      }
+      if (wave != 0) return;
+      if (got) store_row(a.rec, r0, h, lane, o, lse);
+      s_row[0][lane] = o;
+      if (lane == 0) s_lse[0] = lse;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      merge_lds_rows(a, b, h, 1, lane, s_row, s_lse);
+      return;
     }
-    if (n <= kLdsRows) {
+    if (n <= kLdsRows) {  // lane i of a wave: row i * WAVES + wave
+      constexpr int PER = kLdsRows / WAVES;
+      float2 o[PER];
+#pragma unroll
+      for (int i = 0; i < PER; ++i)
+        if (i * WAVES + wave < n)
+          o[i] = reinterpret_cast<const float2*>(
+              a.o_part)[((size_t)(r0 + i * WAVES + wave) * Hq + h) * (kDim / 2) + lane];
+      const int mine = lane * WAVES + wave;
+      const float lse = mine < n ? a.lse_part[(size_t)(r0 + mine) * Hq + h] : 0.0f;
+      const uint64_t got = combine_rows(
+          a.rec, mine < n ? r0 + mine : -1, h, lane, [&](int i, float2 oi, float li) {
+            const int row = i * WAVES + wave;
+            store_row(a.rec, r0 + row, h, lane, oi, li);
+            s_row[row][lane] = oi;
+            if (lane == 0) s_lse[row] = li;
+          });
+#pragma unroll
+      for (int i = 0; i < PER; ++i)
+        if (i * WAVES + wave < n && !((got >> i) & 1)) s_row[i * WAVES + wave][lane] = o[i];
+      if (mine < n && !((got >> lane) & 1)) s_lse[mine] = lse;
       __syncthreads();
       if (wave == 0) merge_lds_rows(a, b, h, n, lane, s_row, s_lse);
       return;
+    }
+    for (int base = 0; base < n; base += 64 * WAVES) {
+      const int first = r0 + base + wave, mine = base + lane * WAVES + wave;
+      combine_rows(a.rec, mine < n ? r0 + mine : -1, h, lane, [&](int i, float2 o, float lse) {
+        store_row(a.rec, first + i * WAVES, h, lane, o, lse);
+      });
     }
     publish_to_workgroup();  // the rows written above, before the merge reads them
   }
@@ -2129,7 +2249,13 @@ hipError_t launch_merge(const MergeArgs& a, hipStream_t stream) {
   if (a.num_seqs == 0 || a.num_q_heads == 0) return hipSuccess;
   const dim3 grid(a.num_q_heads + (a.tail_route ? 1 : 0), a.num_seqs);
   const int rows = a.num_routes / a.num_seqs;  // mean rows per sequence
-  if (a.rec.ml && (rows > 0 ? rows : 1) * a.rec.places <= kRecordsOneWave)
+  // One wave per head leaves no idle waves where grids are large (64 sequences
+  // of 64 heads: step 69.4 us, with four 73.6); in small ones four waves cost
+  // nothing (8 of 32 heads: 24.0 and 24.1) and take a sequence of many rows
+  // faster (16 rows beside 15 sequences, 64 heads: 42.3 and 34.3; 64 rows of
+  // two of 64 sequences, the others empty: 70.5 and 59.2).
+  const bool wide = (int64_t)a.num_seqs * a.num_q_heads > kOneWaveGrid;
+  if (a.rec.ml && wide && (rows > 0 ? rows : 1) * a.rec.places <= kRecordsOneWave)
     hipLaunchKernelGGL(HIP_KERNEL_NAME(merge_kernel<1, true>), grid, dim3(64), 0, stream, a);
   else if (a.rec.ml)
     hipLaunchKernelGGL(HIP_KERNEL_NAME(merge_kernel<4, true>), grid, dim3(256), 0, stream, a);

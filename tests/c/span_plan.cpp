@@ -35,7 +35,21 @@ static int64_t rnd(int64_t lo, int64_t hi) { return std::uniform_int_distributio
     }                                                              \
   } while (0)
 
+// A merge that combines records has one workgroup per (sequence, head): a
+// sequence beside others of at least one route each holds no more rows than the
+// workgroup keeps in LDS, and there is a wave for every 64 rows.
+static int merges() {
+  for (int n = 1; n <= 65535; n += n < 300 ? 1 : 97)
+    for (int r = n; r <= 4 * n + 64 && r <= 65535; ++r)
+      if (kf::merge_combines(r, n) && (r - (n - 1) > kf::kLdsRows || (r + 63) / 64 > n)) {
+        printf("%d routes of %d sequences combined in the merge\n", r, n);
+        return 1;
+      }
+  return 0;
+}
+
 int main(int argc, char** argv) {
+  if (merges()) return 1;
   g_cus = argc > 1 ? atoi(argv[1]) : 256;  // one device per process: the count is cached
   int spans = 0;
   for (int it = 0; it < 4000; ++it) {
