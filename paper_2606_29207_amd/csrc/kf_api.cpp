@@ -271,18 +271,21 @@ SpanPlan plan_span(int32_t num_launch, int32_t num_kv_heads, int32_t group,
   return SpanPlan{};
 }
 
-// The merge of a fused step also combines a split launch's records in small
-// tables where nearly every sequence has one route: 8 chats 24.2 us per step
-// against 26.3 with a combine launch, 64 fp8 sequences 68.6 against 71.7; at
-// 192 sequences the difference is 0.5%.  One workgroup per head takes all rows
-// of a sequence, so with more rows than sequences the combine launch, which
-// spreads them, is as fast (63 rows of 16 sequences 52.9 and 52.8 us) or faster,
-// the more so the more of them one sequence holds (92 rows of 24, 40 of one:
-// 83.9 and 72.1 us; 44 of 8, 37 of one: 37.6 and 31.2; 200 of one, 199 empty
-// sequences beside it: 191.2 and 160.9).  With this bound a sequence beside
-// others of one route or more has at most kLdsRows.
-bool merge_combines(int32_t num_routes, int32_t num_seqs) {
-  return num_routes <= kCombineRows && num_routes < (int64_t)num_seqs + kLdsRows;
+// The merge of a fused step also combines a split launch's records where
+// nearly every sequence has one route: 8 chats 23.9 us per step against 26.3
+// with a combine launch, 64 fp8 sequences 68.3 against 71.7, 217 of 8 heads
+// 28.0 against 30.9; at 192 sequences of 32 heads the difference is 0.5%.  One
+// workgroup per head takes all rows of a sequence, so with more rows than
+// sequences the combine launch, which spreads them, is as fast (63 rows of 16
+// sequences 52.9 and 52.8 us) or faster, the more so the more of them one
+// sequence holds (92 rows of 24, 40 of one: 83.9 and 72.1 us; 44 of 8, 37 of
+// one: 37.6 and 31.2).  With this bound a sequence beside others of one route
+// or more has at most kLdsRows; beside empty ones it may have all, which
+// costs most where one wave takes a head (200 rows 191 us, 161 with a combine
+// launch), so that there the rows are limited too.
+bool merge_combines(int32_t num_routes, int32_t num_seqs, int32_t num_q_heads) {
+  return num_routes < (int64_t)num_seqs + kLdsRows &&
+         (num_routes <= kCombineRows || !wide_merge(num_seqs, num_q_heads));
 }
 
 bool ordered_dispatch(const ChunkPlan& plan, int32_t num_launch, int32_t num_kv_heads,
@@ -607,7 +610,8 @@ int decode_step_impl(const kf_shape* shape, const void* q, void* k_pool, void* v
   ma.page_ids = page_ids;
   ma.num_pages = shape->num_pages;
   ma.num_page_ids = shape->num_page_ids;
-  if ((pa.max_chunks > 1 || pa.span_cols) && kf::merge_combines(num_routes, shape->num_seqs)) {
+  if ((pa.max_chunks > 1 || pa.span_cols) &&
+      kf::merge_combines(num_routes, shape->num_seqs, shape->num_q_heads)) {
     pa.merge_combines = 1;
     ma.rec = kf::records_of(pa);
   }

@@ -22,8 +22,8 @@ constexpr int kMaxLaunchRoutes = 65535;  // routes per launch and KV heads: grid
 constexpr int kChunksOneWave = 8;        // ranges per unit up to which one wave combines a head
 constexpr int64_t kEarlyRecordHeads = 2048;  // most (route, head) pairs whose records load early
 constexpr int kRecordsOneWave = 8;       // mean records per (sequence, head) up to which one wave merges them
-constexpr int64_t kOneWaveGrid = 2048;   // (sequence, head) pairs above which it does
-constexpr int kCombineRows = 80;         // most routes of a fused step whose merge combines records
+constexpr int64_t kOneWaveGrid = 1024;   // (sequence, head) pairs above which it does
+constexpr int kCombineRows = 256;        // most routes of a fused step whose merge combines records one wave a head
 constexpr int kLdsRows = 16;             // rows per sequence that a combining merge keeps in LDS
 constexpr int kLdsStride = kDim + 4;     // padded row of an output buffer in LDS
 constexpr int kSpanRoutes = 1024;        // most routes of a span launch (its table in LDS)
@@ -170,9 +170,13 @@ ChunkPlan plan_chunks(int32_t num_routes, int32_t num_kv_heads, int32_t max_page
 // (1 or 2); route_list: a launch over a route list (kf_partial_attn_subset).
 int32_t units_per_workgroup(bool fp8, bool route_list, const ChunkPlan& plan, int32_t num_launch,
                             int32_t num_kv_heads, int32_t max_pages_per_route);
+// Merges of so many (sequence, head) pairs that one wave each fills the GPU.
+inline bool wide_merge(int32_t num_seqs, int32_t num_q_heads) {
+  return (int64_t)num_seqs * num_q_heads > kOneWaveGrid;
+}
 // Whether the merge kernel of a fused step also combines the records of a
 // split launch.
-bool merge_combines(int32_t num_routes, int32_t num_seqs);
+bool merge_combines(int32_t num_routes, int32_t num_seqs, int32_t num_q_heads);
 // Span launch of num_launch routes: workgroup columns (0: not a span launch)
 // and the workspace it uses.  plan: the launch's chunk plan, which it keeps
 // when its workspace is too small for the spans.

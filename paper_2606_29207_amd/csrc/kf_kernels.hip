@@ -1673,25 +1673,29 @@ __device__ __forceinline__ void store_row(const RecordArgs& a, int r, int h, int
 // Combine up to 64 rows of one query head by one wave: lane i holds launch
 // position u (-1: none).  sink(i, o, lse) takes each row that has records;
 // returns their lanes (the outputs of the others are in place).  Bound by the
-// chain table, (max, sum), outputs of a row, so four rows walk it together,
-// 16 lanes holding the (max, sum) pairs of each; rows of more records go one
-// by one.  combine_unit's sums in combine_unit's order: the same bits.
-template <class Sink>
+// chain table, (max, sum) and outputs of a row, so four rows of up to four
+// records walk it together, 16 lanes holding the (max, sum) pairs of each; a
+// row of more records has loads enough of its own and goes alone.
+// combine_unit's sums in combine_unit's order: the same bits.  MARKS: marks of
+// rows in place are read ahead, one load more in the chain, for tables where
+// most rows may be.
+template <bool MARKS, class Sink>
 __device__ __forceinline__ uint64_t combine_rows(const RecordArgs& a, int u, int h, int lane,
                                                  Sink&& sink) {
-  constexpr int R = 4, K = 64 / R;
+  constexpr int R = 4, K = 4, LANES = 64 / R;
   Pieces p{0, 0, 0};
   if (u >= 0) {
     p = pieces_of(a, u, h);
-    if (p.k > 0 && a.ml[p.rec0 * 2 + 1] == -1.0f) p.k = 0;  // in place (mark_whole)
+    if (MARKS && p.k > 0 && a.ml[p.rec0 * 2 + 1] == -1.0f) p.k = 0;  // mark_whole
   }
+  uint64_t done = 0;
   const int stride = a.span_table ? a.num_kv_heads * a.group : a.group;
   const int rec0 = (int)p.rec0;  // a workspace of 2^31 records would be 1 TB
-  const uint64_t all = __ballot(p.k > 0), many = __ballot(p.k > K);
+  const uint64_t many = __ballot(p.k > K);
   const float2* ml = reinterpret_cast<const float2*>(a.ml);
   const float2* out = reinterpret_cast<const float2*>(a.o) + lane;
-  for (uint64_t left = all & ~many; left;) {
-    int row[R], rec[R], k[R], cnt = 0, kmax = 0;
+  for (uint64_t left = __ballot(p.k > 0) & ~many; left;) {
+    int row[R], rec[R], k[R], cnt = 0;
 #pragma unroll
     for (int s = 0; s < R; ++s) {  // places past the last row repeat the first
       row[s] = left ? __builtin_ctzll(left) : row[0];
@@ -1699,21 +1703,17 @@ __device__ __forceinline__ uint64_t combine_rows(const RecordArgs& a, int u, int
       left &= left - 1;
       rec[s] = __builtin_amdgcn_readlane(rec0, row[s]);
       k[s] = __builtin_amdgcn_readlane(p.k, row[s]);
-      kmax = max(kmax, k[s]);
     }
-    const int ms = lane / K, mi = lane % K;
+    const int ms = lane / LANES, mi = lane % LANES;
     const bool in = mi < pick4(k[0], k[1], k[2], k[3], ms);
     const float2 r = in ? ml[pick4(rec[0], rec[1], rec[2], rec[3], ms) + (size_t)mi * stride]
                         : make_float2(neg_inf(), 0.0f);
-    float2 v[R][4], acc[R][4];
-    auto load = [&](int j) {
+    float2 v[R][K];
 #pragma unroll
-      for (int s = 0; s < R; ++s)
+    for (int s = 0; s < R; ++s)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          v[s][q] = out[(rec[s] + (size_t)min(j + q, k[s] - 1) * stride) * (kDim / 2)];
-    };
-    load(0);
+      for (int q = 0; q < K; ++q)
+        v[s][q] = out[(rec[s] + (size_t)min(q, k[s] - 1) * stride) * (kDim / 2)];
     float M = r.x;
 #pragma unroll
     for (int m = K / 2; m >= 1; m >>= 1) M = fmaxf(M, __shfl_xor(M, m));
@@ -1723,32 +1723,21 @@ __device__ __forceinline__ uint64_t combine_rows(const RecordArgs& a, int u, int
     for (int m = K / 2; m >= 1; m >>= 1) L += __shfl_xor(L, m);
     const uint64_t used = __ballot(r.x != neg_inf());
 #pragma unroll
-    for (int s = 0; s < R; ++s)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) acc[s][q] = make_float2(0.0f, 0.0f);
-    for (int j = 0; j < kmax; j += 4) {
-      if (j > 0) load(j);
-#pragma unroll
-      for (int s = 0; s < R; ++s)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int i = K * s + j + q;
-          const bool has = (used >> i) & 1;
-          const float wj = has ? read_lane(w, i) : 0.0f;
-          acc[s][q].x = __builtin_fmaf(wj, has ? v[s][q].x : 0.0f, acc[s][q].x);
-          acc[s][q].y = __builtin_fmaf(wj, has ? v[s][q].y : 0.0f, acc[s][q].y);
-        }
-    }
-#pragma unroll
     for (int s = 0; s < R; ++s) {
       if (s >= cnt) break;
-      float2 t = acc[s][0];
+      if (read_lane(r.y, LANES * s) == -1.0f) continue;  // in place
+      done |= 1ull << row[s];
+      float2 t = make_float2(0.0f, 0.0f);
 #pragma unroll
-      for (int q = 1; q < 4; ++q) {
-        t.x += acc[s][q].x;
-        t.y += acc[s][q].y;
+      for (int q = 0; q < K; ++q) {
+        const int i = LANES * s + q;
+        const bool has = (used >> i) & 1;
+        const float wj = has ? read_lane(w, i) : 0.0f;
+        // a subset's only record, rounded before it is added
+        t.x += __builtin_fmaf(wj, has ? v[s][q].x : 0.0f, 0.0f);
+        t.y += __builtin_fmaf(wj, has ? v[s][q].y : 0.0f, 0.0f);
       }
-      const float Ls = read_lane(L, K * s), Ms = read_lane(M, K * s);
+      const float Ls = read_lane(L, LANES * s), Ms = read_lane(M, LANES * s);
       sink(row[s], make_float2(t.x / Ls, t.y / Ls), (Ms + __log2f(Ls)) * kLn2);
     }
   }
@@ -1756,12 +1745,14 @@ __device__ __forceinline__ uint64_t combine_rows(const RecordArgs& a, int u, int
     const int i = __builtin_ctzll(left);
     float2 o;
     float lse;
-    combine_unit<1>(a, {(size_t)__builtin_amdgcn_readlane(rec0, i), stride,
-                        __builtin_amdgcn_readlane(p.k, i)},
-                    lane, 0, nullptr, o, lse);
+    if (!combine_unit<1>(a, {(size_t)__builtin_amdgcn_readlane(rec0, i), stride,
+                             __builtin_amdgcn_readlane(p.k, i)},
+                         lane, 0, nullptr, o, lse))
+      continue;
+    done |= 1ull << i;
     sink(i, o, lse);
   }
-  return all;
+  return done;
 }
 
 // Small and bound by its chain of dependent loads, so the chain is short:
@@ -2030,7 +2021,7 @@ __device__ __forceinline__ void step_bookkeeping(const MergeArgs& a, int b, int 
     }
     if (__ballot(orphan) == 0) return;
     for (int h = id / blocks; h < a.num_q_heads; h += share)
-      combine_rows(a.rec, orphan ? u : -1, h, lane, [&](int i, float2 o, float lse) {
+      combine_rows<true>(a.rec, orphan ? u : -1, h, lane, [&](int i, float2 o, float lse) {
         store_row(a.rec, id % blocks * 64 + i, h, lane, o, lse);
       });
   }
@@ -2068,13 +2059,13 @@ __global__ __launch_bounds__(64 * WAVES) void merge_kernel(MergeArgs a) {
     __shared__ float s_lse[kLdsRows];
     const int n = r1 - r0;
     if (n == 1) {
-      const Pieces p = pieces_of(a.rec, r0, h);
-      const bool share = WAVES == 4 && p.k > kRecordsOneWave;
-      if (wave != 0 && !share) return;
       const size_t row = (size_t)r0 * Hq + h;
       // a whole unit's row is in place; its loads go out with the records'
       float2 o = reinterpret_cast<const float2*>(a.o_part)[row * (kDim / 2) + lane];
       float lse = a.lse_part[row];
+      const Pieces p = pieces_of(a.rec, r0, h);
+      const bool share = WAVES == 4 && p.k > kRecordsOneWave;
+      if (wave != 0 && !share) return;
       const bool got = WAVES == 4 && share
                            ? combine_unit<WAVES>(a.rec, p, lane, wave, s_rec, o, lse)
                            : combine_unit<1>(a.rec, p, lane, wave, s_rec, o, lse);
@@ -2096,7 +2087,7 @@ __global__ __launch_bounds__(64 * WAVES) void merge_kernel(MergeArgs a) {
               a.o_part)[((size_t)(r0 + i * WAVES + wave) * Hq + h) * (kDim / 2) + lane];
       const int mine = lane * WAVES + wave;
       const float lse = mine < n ? a.lse_part[(size_t)(r0 + mine) * Hq + h] : 0.0f;
-      const uint64_t got = combine_rows(
+      const uint64_t got = combine_rows<false>(
           a.rec, mine < n ? r0 + mine : -1, h, lane, [&](int i, float2 oi, float li) {
             const int row = i * WAVES + wave;
             store_row(a.rec, r0 + row, h, lane, oi, li);
@@ -2113,7 +2104,7 @@ __global__ __launch_bounds__(64 * WAVES) void merge_kernel(MergeArgs a) {
     }
     for (int base = 0; base < n; base += 64 * WAVES) {
       const int first = r0 + base + wave, mine = base + lane * WAVES + wave;
-      combine_rows(a.rec, mine < n ? r0 + mine : -1, h, lane, [&](int i, float2 o, float lse) {
+      combine_rows<true>(a.rec, mine < n ? r0 + mine : -1, h, lane, [&](int i, float2 o, float lse) {
         store_row(a.rec, first + i * WAVES, h, lane, o, lse);
       });
     }
@@ -2250,12 +2241,11 @@ hipError_t launch_merge(const MergeArgs& a, hipStream_t stream) {
   const dim3 grid(a.num_q_heads + (a.tail_route ? 1 : 0), a.num_seqs);
   const int rows = a.num_routes / a.num_seqs;  // mean rows per sequence
   // One wave per head leaves no idle waves where grids are large (64 sequences
-  // of 64 heads: step 69.4 us, with four 73.6); in small ones four waves cost
-  // nothing (8 of 32 heads: 24.0 and 24.1) and take a sequence of many rows
-  // faster (16 rows beside 15 sequences, 64 heads: 42.3 and 34.3; 64 rows of
-  // two of 64 sequences, the others empty: 70.5 and 59.2).
-  const bool wide = (int64_t)a.num_seqs * a.num_q_heads > kOneWaveGrid;
-  if (a.rec.ml && wide && (rows > 0 ? rows : 1) * a.rec.places <= kRecordsOneWave)
+  // of 64 heads: step 68.3 us, with four 73.6; 217 of 8: 28.0 and 29.2); in
+  // small ones four waves cost nothing (8 of 32 heads: 23.9 and 24.0) and take
+  // a sequence of many rows faster (16 rows beside 15 sequences, 64 heads: 33.6
+  // and 40.9).
+  if (a.rec.ml && wide_merge(a.num_seqs, a.num_q_heads) && (rows > 0 ? rows : 1) * a.rec.places <= kRecordsOneWave)
     hipLaunchKernelGGL(HIP_KERNEL_NAME(merge_kernel<1, true>), grid, dim3(64), 0, stream, a);
   else if (a.rec.ml)
     hipLaunchKernelGGL(HIP_KERNEL_NAME(merge_kernel<4, true>), grid, dim3(256), 0, stream, a);

@@ -41,7 +41,7 @@ static int64_t rnd(int64_t lo, int64_t hi) { return std::uniform_int_distributio
 static int merges() {
   for (int n = 1; n <= 65535; n += n < 300 ? 1 : 97)
     for (int r = n; r <= 4 * n + 64 && r <= 65535; ++r)
-      if (kf::merge_combines(r, n) && (r - (n - 1) > kf::kLdsRows || (r + 63) / 64 > n)) {
+      if (kf::merge_combines(r, n, 1) && (r - (n - 1) > kf::kLdsRows || (r + 63) / 64 > n)) {
         printf("%d routes of %d sequences combined in the merge\n", r, n);
         return 1;
       }
