@@ -201,22 +201,33 @@ int32_t units_per_workgroup(bool fp8, bool route_list, const ChunkPlan& plan, in
 }
 
 // Whether a launch of num_launch routes runs as spans, whatever its workspace.
-// Measured against the chunk plan, both with the combining merge, one box:
-//  - Ragged tables: 4-16 sequences of 300-4000 tokens and 8 KV heads -29 to
-//    -37% (48.2 -> 36.7 us at 139 MB, fp8 42.2 -> 30.0 us), 64 of 300-3000
-//    -20%, 12 of 20000-60000 -9 to -26%, 192 of 65-1100 -5 to -16%, the
-//    agentic batch (1208 units, 7.7 GB) -1.5%; the one larger batch that lost
-//    did so by 1.6% (256 of 300-6000 tokens, 2.0 GB).  Below two tiles per
-//    wave the parts cost more than the balance gives (8 sequences of 300-3000
-//    tokens 20.2 -> 22.0 us), and so they do with routes of at most 32 pages
-//    and more than 8 query heads per KV head (250 of 100-260 tokens, 16 heads:
-//    46.5 -> 49.0 us).
+// Measured against the chunk plan, partial attention and its combine, one box:
+//  - Ragged tables that the chunk plan splits: 16-256 sequences of 100-8000
+//    tokens, 8 KV heads of 4 query heads or 4 of 16, bf16 -1 to -50%, fp8 -2 to
+//    -57%, 12 sequences of 20000-60000 -9 to -26%, the agentic batch (1208
+//    units, 7.7 GB) -2.5%.  Below two tiles per wave the parts cost more than
+//    the balance gives (8 sequences of 300-3000 tokens 20.2 -> 22.0 us), and
+//    so they do with routes of at most 32 pages and more than 8 query heads
+//    per KV head (250 of 100-260 tokens, 16 heads: 46.5 -> 49.0 us).
+//  - Ragged tables that it leaves whole (bf16 units of at most 256 pages that
+//    fill a round, or very many) wait for their longest units only, in a launch
+//    without a combine: spans pay where the pages that the routes' reserves
+//    fall short of the longest come to 30 a slot, or 50 with more than 8 query
+//    heads per KV head, whose parts are larger.  Of 231 such tables (64-250
+//    sequences of 30-3900 tokens, 4 to 32 KV heads, groups of 1 to 16) those
+//    at the line or above gain 0-21%, but for 12 that lose 0.3-8% (65 x 8 heads of
+//    500-1500 tokens 51.3 -> 53.8 us, 96 x 12 of 65-500 37.8 -> 40.7); below
+//    it 64 x 8 heads of 500-1024 tokens lost 8%, 128 x 4 of 16 query heads
+//    17%, 96 x 8 of 400-500 29%, and some gain (65 x 8 of 1000-1500: 8%).
 //  - Equal tables whose chunk plan keeps units whole (they fill the GPU
 //    evenly, or are short) stay as they are: 2000 fp8 units of 44 or 125 pages
 //    lose 5-7%, 512 units 1-4%.  Split ones run as spans when units outnumber
-//    the slots (640 to 3000 units, 44 to 375 pages: bf16 -1 to -15%, fp8 0 to
-//    -30%), or the compute units without their ranges filling them evenly
-//    (400 units: -2 to -18%; 320 and 384 units, whose ranges do, -4 to +3%).
+//    the slots (520 to 3000 units, 44 to 375 pages: bf16 +0.5 to -16%, fp8 -1
+//    to -34%), or the compute units without their ranges filling these evenly:
+//    288, 400 and 416 units -1 to -25%, and bf16 320 and 352 units, whose
+//    ranges leave the last quarter of them empty, -3.6 to 0%; fp8 ones of
+//    these lose (352 units of 250 pages 74.0 -> 77.7 us), unless more than four
+//    ranges run on each.
 // Launches over a route list keep the chunk plan: the page table does not
 // describe their routes.
 namespace {
@@ -227,10 +238,16 @@ bool span_launch(int32_t num_launch, int32_t num_kv_heads, int32_t group,
   const int64_t tile = fp8 ? 4 : 2, units = (int64_t)num_launch * num_kv_heads;
   if (num_launch * (((int64_t)max_pages_per_route + tile - 1) / tile) > INT32_MAX) return false;
   if ((int64_t)num_page_ids * num_kv_heads < 2 * tile * slots * kWaves) return false;
-  if (ragged_table(num_page_ids, num_launch, max_pages_per_route))
+  if (ragged_table(num_page_ids, num_launch, max_pages_per_route)) {
+    // units < 2^26, pages < 2^31
+    const int64_t spare = units * max_pages_per_route - (int64_t)num_page_ids * num_kv_heads;
+    if (plan.max_chunks == 1 && spare < (group <= 8 ? 30 : 50) * slots) return false;
     return max_pages_per_route > 32 || group <= 8;
-  return plan.max_chunks > 1 &&
-         (units > slots || (units > slots / 2 && units * plan.max_chunks % (slots / 2) != 0));
+  }
+  if (plan.max_chunks == 1) return false;
+  const int64_t cus = slots / 2, items = units * plan.max_chunks, rem = items % cus;
+  if (units <= cus || rem == 0) return units > slots;
+  return units > slots || !fp8 || rem * 4 < cus * 3 || items > 4 * cus;
 }
 }  // namespace
 

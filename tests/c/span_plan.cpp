@@ -48,8 +48,42 @@ static int merges() {
   return 0;
 }
 
+// Tables on either side of the launch rule's lines (256 compute units).
+static int rules() {
+  struct {
+    int R, H, G, pages, ids;
+    bool fp8, span;
+  } t[] = {
+      {192, 32, 1, 81, 8400, false, true},   // whole units, long reserves beside short ones
+      {64, 8, 4, 64, 3072, false, false},    // whole units, near their longest: 16 pages a slot
+      {64, 8, 4, 94, 6016 - 1920, false, true},      // 30 pages a slot
+      {64, 8, 4, 94, 6016 - 1919, false, false},
+      {64, 8, 16, 125, 8000 - 3200, false, true},    // 50 with 16 query heads per KV head
+      {64, 8, 16, 125, 8000 - 3199, false, false},
+      {64, 8, 4, 600, 20000, false, true},   // ragged and split
+      {40, 8, 4, 500, 20000, false, true},   // 320 equal units in 3 ranges: 960 on 256 CUs
+      {40, 8, 4, 500, 20000, true, false},
+      {44, 8, 4, 500, 22000, true, false},   // 352 in 2: 704
+      {50, 8, 4, 500, 25000, true, true},    // 400 in 5: 2000, more than four each
+      {48, 8, 4, 500, 24000, false, false},  // 384 in 2: 768, three each
+      {65, 8, 4, 500, 32500, true, true},    // 520 units: more than slots
+  };
+  for (const auto& c : t) {
+    const kf::ChunkPlan plan =
+        kf::plan_chunks(c.R, c.H, c.pages, kf::ragged_table(c.ids, c.R, c.pages), c.fp8, false);
+    const bool got = kf::plan_span(c.R, c.H, c.G, c.pages, c.ids, c.fp8, false, plan, 512).wg_cols > 0;
+    if (got != c.span) {
+      printf("R=%d H=%d G=%d pages=%d ids=%d fp8=%d (plan %d ranges): span %d\n", c.R, c.H, c.G, c.pages,
+             c.ids, c.fp8, plan.max_chunks, got);
+      return 1;
+    }
+  }
+  return 0;
+}
+
 int main(int argc, char** argv) {
   if (merges()) return 1;
+  if (argc == 1 && rules()) return 1;
   g_cus = argc > 1 ? atoi(argv[1]) : 256;  // one device per process: the count is cached
   int spans = 0;
   for (int it = 0; it < 4000; ++it) {
