@@ -488,15 +488,22 @@ __device__ __forceinline__ void reset(Attn& s) {
 // the page's K scale), vs: V scale, of the lane's page; tok0: the lane's
 // first route-local token, lim: the token bound.  MASK: the tile can hold
 // slots past the bound; their V bits are zeroed and they add nothing.
-// TILE_SUM: the tile's p.V is summed from zero and then added, one rounding of
-// the running output per tile instead of two: a bf16 span wave's chains
-// are several times as long as a chunk wave's, and its error stays at theirs
-// (agentic batch 9.6e-7 against 8.9e-7; 1.1e-6 without).  The add takes the
-// place of the rescaling product, so it costs no time; fp8 tiles have no
-// registers to spare for it, and their error is the bf16 pair's (5e-6).
-template <bool FP8, bool MASK, bool TILE_SUM = false>
+// SPAN: a span wave's chains are several times as long as a chunk wave's, so
+// its terms are rounded less.  The tile's sum of p, and for bf16 its p.V, start
+// from zero and are then added, one rounding of the running sum per tile
+// instead of one per pair of slots or matrix product, and the bf16 p (at most
+// 1, so it cannot round up to infinity) is split into its nearest bf16 and the
+// rest, half the error of the truncated split.  The adds take the place of the
+// rescaling product, so none of it costs time (237.96 -> 238.0 us, 61.2 ->
+// 61.3, 1165.8 -> 1164.8); fp8 tiles have no registers to spare for p.V.
+// Error of the partials against 64 bits with the chunk plan, and as spans
+// without and with it: 192 multi-head sequences 2.88e-7, 3.29e-7, 2.28e-7, 24
+// of 16 heads per KV head 5.2e-7, 5.5e-7, 3.4e-7, the agentic batch 8.3e-7,
+// 9.3e-7, 5.8e-7; fp8 batches 5.2 to 5.5e-6 in all three, the split's.
+template <bool FP8, bool MASK, bool SPAN = false>
 __device__ __forceinline__ void attend(const TileRaw<FP8>& t, const u32x4 (&qb)[4], float ks,
                                        float vs, int tok0, int lim, Attn& st) {
+  constexpr bool TILE_SUM = SPAN && !FP8;
   constexpr int NC = Geo<FP8>::NC, NH = Geo<FP8>::NH;
   // ---- S^T = K Q^T (fp8 codes widen to bf16 right before their MFMA)
   f32x4 s[NC];
@@ -530,7 +537,7 @@ __device__ __forceinline__ void attend(const TileRaw<FP8>& t, const u32x4 (&qb)[
   const float m_new = fmaxf(st.m, mt);
   const float alpha = exp2_fast(st.m - m_new);
   st.m = m_new;
-  st.l *= alpha;
+  if constexpr (!SPAN) st.l *= alpha;
   if constexpr (!TILE_SUM) {
 #pragma unroll
     for (int b8 = 0; b8 < 8; ++b8) st.o[b8] *= alpha;
@@ -539,6 +546,7 @@ __device__ __forceinline__ void attend(const TileRaw<FP8>& t, const u32x4 (&qb)[
   // ---- P^T operands: half h2 holds slots 8*h2 + j (j < 8) of the lane's
   // range, i.e. MFMA c = 2*h2 + j/4, row r4 = j%4; bf16 hi + lo
   u32x4 phi[NH], plo[NH];
+  float sum_l = 0.0f;  // SPAN: of the tile
 #pragma unroll
   for (int h2 = 0; h2 < NH; ++h2)
 #pragma unroll
@@ -546,19 +554,28 @@ __device__ __forceinline__ void attend(const TileRaw<FP8>& t, const u32x4 (&qb)[
       const int cc = 2 * h2 + (jj >> 1), r4 = 2 * (jj & 1);
       const float e0 = exp2_fast(s[cc][r4] - m_new);
       const float e1 = exp2_fast(s[cc][r4 + 1] - m_new);
-      st.l += e0 + e1;
+      (SPAN ? sum_l : st.l) += e0 + e1;
       float x0 = e0 * vs, x1 = e1 * vs;
       if constexpr (MASK && FP8) {  // a masked slot adds nothing, whatever its page's scales
         const int t0 = tok0 + 8 * h2 + 2 * jj;
         x0 = t0 < lim ? x0 : 0.0f;
         x1 = t0 + 1 < lim ? x1 : 0.0f;
       }
-      const uint32_t b0 = __builtin_bit_cast(uint32_t, x0) & 0xFFFF0000u;
-      const uint32_t b1 = __builtin_bit_cast(uint32_t, x1) & 0xFFFF0000u;
-      phi[h2][jj] = (b0 >> 16) | b1;
+      uint32_t b0, b1;
+      if constexpr (TILE_SUM) {
+        phi[h2][jj] = pack_bf16_rne(x0, x1);
+        b0 = phi[h2][jj] << 16;
+        b1 = phi[h2][jj] & 0xFFFF0000u;
+      } else {
+        b0 = __builtin_bit_cast(uint32_t, x0) & 0xFFFF0000u;
+        b1 = __builtin_bit_cast(uint32_t, x1) & 0xFFFF0000u;
+        phi[h2][jj] = (b0 >> 16) | b1;
+      }
       plo[h2][jj] = pack_bf16_rne(x0 - __builtin_bit_cast(float, b0),
                                   x1 - __builtin_bit_cast(float, b1));
     }
+
+  if constexpr (SPAN) st.l = __builtin_fmaf(st.l, alpha, sum_l);
 
   // ---- O^T += V^T P^T; V of slots past the range is zeroed (unused slots
   // may hold anything)
@@ -1318,7 +1335,7 @@ __global__ __launch_bounds__(kThreads, 2) void span_kernel(PartialArgs a) {
         vs = x.vs;
       }
       marks |= ti.uf;
-      attend<FP8, false, !FP8>(x, qb, ks, vs, tok0, ti.left, acc);
+      attend<FP8, false, true>(x, qb, ks, vs, tok0, ti.left, acc);
     };
     // end of a part: write the route, or hand the part to the workgroup
     auto finish = [&](const SpanTile& ti) {
@@ -1331,6 +1348,12 @@ __global__ __launch_bounds__(kThreads, 2) void span_kernel(PartialArgs a) {
         m = qnan();
         if (lane == 0) atomicOr(a.err_flags, KF_EFLAG_BAD_PAGE);
       }
+      // The lane's place, opaque to the compiler: addresses formed from the
+      // loop's own would be hoisted out of it and spilled, and their reload
+      // here waits for the tiles in flight.
+      int lo = lane;
+      asm volatile("" : "+v"(lo));
+      const int li = lo & 15, grp = lo >> 4;
       if (pb >= t0 && pe <= t1) {
         const int r = a.route_list ? as_const(a.route_list)[pu] : pu;
         const size_t row = (size_t)r * Hq + hq0 + li;

@@ -75,6 +75,33 @@ def test_span_launch_matches_oracle_and_chunk_plan(gpu, case):
     assert (lse_part[both] - st.lse_part[both]).abs().max() <= 2e-5
 
 
+@pytest.mark.parametrize("case,bound", [
+    # multi-head, columns of many short routes; long columns of one route
+    ((32, 32, False, [65 + 23 * i for i in range(40)], 65536), 1.0),
+    ((64, 4, False, [40000, 30000, 20000, 500, 12000], 65536), 1.0),
+    # fp8: nearly all of the error is that of the split of p, the same in both
+    ((16, 2, True, [60000, 45000, 31000, 700], 65536), 1.01),
+], ids=["mha", "gqa16", "fp8"])
+def test_span_error_is_no_larger_than_the_chunk_plans(gpu, case, bound):
+    """A span wave sums runs several times as long as a chunk wave's in
+    float32; the partials stay no further from float64 than the chunk plan's."""
+    import torch
+    from paper_2606_29207_amd import kf
+    inst = _instance(case, steps=1, seed=9)
+    assert _is_span(inst)
+    o = run_oracle(inst, 1)
+    st = run_gpu(inst, 1)
+    ref = torch.from_numpy(o["o_part"]).to(st.device)
+    ident = torch.arange(len(inst.routes), dtype=torch.int32, device=st.device)
+    err = [float((st.o_part.double() - ref).norm() / ref.norm())]
+    kf.partial_attn(st.shape, st.q, st.k_pool, st.v_pool, st.routes, st.max_pages_per_route,
+                    st.page_ids, st.o_part, st.lse_part, st.workspace, st.err_flags,
+                    k_scale=st.k_scale, v_scale=st.v_scale, route_list=ident)
+    err.append(float((st.o_part.double() - ref).norm() / ref.norm()))
+    print(f"[spans] error {err[0]:.3e}, chunk plan {err[1]:.3e}", flush=True)
+    assert err[0] <= bound * err[1], err
+
+
 def test_span_step_without_a_workspace_is_the_same(gpu):
     import torch
     from paper_2606_29207_amd.step import DecodeState
