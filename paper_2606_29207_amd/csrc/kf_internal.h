@@ -27,7 +27,8 @@ constexpr int kCombineRows = 256;        // most routes of a fused step whose me
 constexpr int kLdsRows = 16;             // rows per sequence that a combining merge keeps in LDS
 constexpr int kLdsStride = kDim + 4;     // padded row of an output buffer in LDS
 constexpr int kSpanRoutes = 1024;        // most routes of a span launch (its table in LDS)
-constexpr size_t kSpanLds = 80 << 10;    // most LDS of its workgroups: two per compute unit
+constexpr size_t kSpanStaticLds = 64;    // its workgroups' LDS besides span_lds_bytes
+constexpr size_t kSpanLds = (80 << 10) - kSpanStaticLds;  // most of these: two workgroups per compute unit
 constexpr int kMergeRowsFourWaves = 8;   // mean rows per sequence from which four waves merge a head
 constexpr int kOrderBuckets = 64;        // range-size classes of the dispatch order
 constexpr int64_t kMaxOrderItems = int64_t(1) << 20;  // largest split launch given a dispatch order
@@ -132,7 +133,7 @@ inline RecordArgs records_of(const PartialArgs& a) {
           span ? a.span_table : nullptr};
 }
 
-// LDS of a span workgroup: the parts of its columns and the route table.
+// Dynamic LDS of a span workgroup: the parts of its columns and the route table.
 inline size_t span_lds_bytes(int32_t group, int32_t num_launch) {
   return sizeof(float) * ((size_t)2 * kWaves * group * (kLdsStride + 2) + 4 * (size_t)num_launch + 1);
 }

@@ -1100,6 +1100,7 @@ __global__ __launch_bounds__(kThreads, 2) void span_kernel(PartialArgs a) {
   extern __shared__ f32x4 s_lds[];
   float* s_dyn = reinterpret_cast<float*>(s_lds);  // parts: [2 * kWaves][G][kLdsStride], (max, sum)
   __shared__ int s_sum[kWaves], s_start[kWaves], s_part[2 * kWaves];
+  static_assert(sizeof(s_sum) + sizeof(s_start) + sizeof(s_part) == kSpanStaticLds, "");
   const int U = a.num_units_routes, H = a.num_kv_heads, G = a.group, Hq = a.num_q_heads;
   const int tid = threadIdx.x, lane = tid & 63, grp = lane >> 4, li = lane & 15;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1117,15 +1118,12 @@ __global__ __launch_bounds__(kThreads, 2) void span_kernel(PartialArgs a) {
     const int u = tid * per + i;
     cnt[i] = 0;
     if (i < per && u < U) {
-      const int r = a.route_list ? a.route_list[u] : u;
-      RouteView rv{};
-      bool listed = r >= 0 && r < a.num_routes;
-      if (listed) rv = read_route(a, r);
-      if (listed && !rv.bad) cnt[i] = (rv.npages + TP - 1) / TP;
+      const RouteView rv = read_route(a, u);
+      if (!rv.bad) cnt[i] = (rv.npages + TP - 1) / TP;
       s_base[u] = rv.base;
       s_n[u] = rv.bad && rv.n == 0 ? -1 : rv.n;  // 0: empty
       s_seq[u] = rv.app ? ~rv.seq : cnt[i] ? rv.seq : 0;
-      if (blockIdx.x == 0 && (!listed || rv.bad)) atomicOr(a.err_flags, KF_EFLAG_BAD_ROUTE);
+      if (blockIdx.x == 0 && rv.bad) atomicOr(a.err_flags, KF_EFLAG_BAD_ROUTE);
       sum += cnt[i];
     }
   }
@@ -1171,12 +1169,10 @@ __global__ __launch_bounds__(kThreads, 2) void span_kernel(PartialArgs a) {
   // ---- outputs of routes without tiles (empty or bad), spread over the workgroups
   for (int u = blockIdx.x; u < U; u += gridDim.x) {
     if (s_pre[u + 1] != s_pre[u]) continue;
-    const int r = a.route_list ? a.route_list[u] : u;
-    if (r < 0 || r >= a.num_routes) continue;
     const bool bad = s_n[u] != 0;
     const float ov = bad ? qnan() : 0.0f, lv = bad ? qnan() : neg_inf();
-    for (int e = tid; e < Hq * kDim; e += kThreads) a.o_part[(size_t)r * Hq * kDim + e] = ov;
-    for (int h = tid; h < Hq; h += kThreads) a.lse_part[(size_t)r * Hq + h] = lv;
+    for (int e = tid; e < Hq * kDim; e += kThreads) a.o_part[(size_t)u * Hq * kDim + e] = ov;
+    for (int h = tid; h < Hq; h += kThreads) a.lse_part[(size_t)u * Hq + h] = lv;
   }
 
   // ---- this wave's column
@@ -1355,8 +1351,7 @@ __global__ __launch_bounds__(kThreads, 2) void span_kernel(PartialArgs a) {
       asm volatile("" : "+v"(lo));
       const int li = lo & 15, grp = lo >> 4;
       if (pb >= t0 && pe <= t1) {
-        const int r = a.route_list ? as_const(a.route_list)[pu] : pu;
-        const size_t row = (size_t)r * Hq + hq0 + li;
+        const size_t row = (size_t)pu * Hq + hq0 + li;
         if (li < G) {
           const float lw = m != m ? qnan() : l;
 #pragma unroll
@@ -1453,7 +1448,6 @@ __global__ __launch_bounds__(kThreads, 2) void span_kernel(PartialArgs a) {
     done = u;
     const bool whole = s_pre[u] >= wt0 && s_pre[u + 1] <= wt1;
     const size_t rec = ((size_t)(blk + min(u, sc.of(s_pre[u]) / kWaves)) * H + g) * G;
-    const int r = a.route_list ? as_const(a.route_list)[u] : u;
 #pragma unroll 1
     for (int e = tid; e < G * (kDim / 4); e += kThreads) {  // four dims of one head
       const int h = e / (kDim / 4), d = e % (kDim / 4) * 4;
@@ -1476,7 +1470,7 @@ __global__ __launch_bounds__(kThreads, 2) void span_kernel(PartialArgs a) {
           O += wt * *reinterpret_cast<const f32x4*>(s_dyn + (k * G + h) * kLdsStride + d);
         }
       if (whole) {
-        const size_t row = (size_t)r * Hq + hq0 + h;
+        const size_t row = (size_t)u * Hq + hq0 + h;
         *reinterpret_cast<f32x4*>(a.o_part + row * kDim + d) = O / L;
         if (d == 0) a.lse_part[row] = (M + __log2f(L)) * kLn2;
       } else {

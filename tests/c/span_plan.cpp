@@ -67,6 +67,10 @@ static int rules() {
       {50, 8, 4, 500, 25000, true, true},    // 400 in 5: 2000, more than four each
       {48, 8, 4, 500, 24000, false, false},  // 384 in 2: 768, three each
       {65, 8, 4, 500, 32500, true, true},    // 520 units: more than slots
+      {827, 2, 16, 500, 200000, true, true},  // 16 query heads: the table fits LDS
+      {828, 2, 16, 500, 200000, true, false},
+      {1024, 2, 15, 500, 200000, true, true},
+      {1025, 2, 4, 500, 200000, true, false},
   };
   for (const auto& c : t) {
     const kf::ChunkPlan plan =
@@ -98,7 +102,9 @@ int main(int argc, char** argv) {
     const kf::SpanPlan p = kf::plan_span(R, H, G, maxp, s.num_page_ids, fp8, list, c, slots);
     if (!p.wg_cols) continue;
     ++spans;
-    CHECK(!list && R <= kf::kSpanRoutes && kf::span_lds_bytes(G, R) <= kf::kSpanLds);
+    // two workgroups fit the 160 KiB of a compute unit
+    CHECK(!list && R <= kf::kSpanRoutes &&
+          2 * (kf::span_lds_bytes(G, R) + kf::kSpanStaticLds) <= 160 << 10);
     CHECK((int64_t)p.wg_cols * H <= std::max<int64_t>(slots, H));
     CHECK(p.total <= KF_SCRATCH_BYTES);
     CHECK(p.total <= kf_partial_attn_workspace_bytes(&s, R, maxp));
