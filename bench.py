@@ -237,6 +237,9 @@ def kernel_label(st, wl, route_list=None) -> str:
     workgroup and any combine launch."""
     from paper_2606_29207_amd import kf
     n = st.routes.shape[0] if route_list is None else len(route_list)
+    cols = kf.partial_attn_spans(st.shape, n, st.max_pages_per_route, route_list is not None)
+    if cols:
+        return f"span_kernel<{wl.kv_dtype}> + combine_kernel ({cols} workgroup columns per KV head)"
     chunk_pages, max_chunks, units = kf.partial_attn_plan(st.shape, n, st.max_pages_per_route,
                                                           route_list=route_list is not None)
     name = f"partial_kernel<{wl.kv_dtype}" + (", 2 units/workgroup>" if units == 2 else ">")

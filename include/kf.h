@@ -147,8 +147,11 @@ int kf_kv_append(const kf_shape* shape, void* k_pool, void* v_pool, float* k_sca
  * unit is split over several workgroups whose partials go through this
  * workspace; a split launch of at least two rounds of resident
  * workgroups also keeps its dispatch order there (8 bytes per work item, a
- * table that a one-workgroup kernel writes before the partial kernel).  The
- * size covers every launch of at most `num_routes` routes, so a workspace
+ * table that a one-workgroup kernel writes before the partial kernel), and
+ * launches that run as spans (kf_partial_attn_spans) their table and the
+ * records of cut routes, within the same size.  A launch may use all of the
+ * workspace that it is given, so launches that may overlap need workspaces of
+ * their own.  The size covers every launch of at most `num_routes` routes, so a workspace
  * sized for a route table also serves
  * kf_partial_attn_subset over any part of it, and it covers ragged and
  * equal routes alike: it does not depend on shape->num_page_ids, so it stays
@@ -166,11 +169,14 @@ size_t kf_partial_attn_workspace_bytes(const kf_shape* shape, int32_t num_routes
  * kf_partial_attn and kf_decode_step (route_list_launch = 0), or
  * kf_partial_attn_subset over a list of num_launch routes
  * (route_list_launch = 1).  Not an operation of the paper: a description of
- * this implementation's launch, for callers that size or inspect it.
+ * this implementation's launch, for callers that size or inspect it.  Where
+ * kf_partial_attn_spans reports columns the launch runs as spans, and this
+ * plan only with a workspace too small for their records.
  *   *chunk_pages  pages per workgroup range; a unit of n pages is cut into
  *                 ceil(n / chunk_pages) ranges
  *   *max_chunks   most ranges per unit; 1 = every unit whole, no combine
- *                 launch and no workspace use.  A split launch whose
+ *                 launch and no workspace use (spans use both).  A split
+ *                 launch whose
  *                 max_chunks * num_kv_heads * num_launch work items reach
  *                 two per resident workgroup slot (two slots per compute
  *                 unit) and stay within 2^20 is dispatched largest ranges
@@ -195,6 +201,28 @@ size_t kf_partial_attn_workspace_bytes(const kf_shape* shape, int32_t num_routes
 int kf_partial_attn_plan(const kf_shape* shape, int32_t num_launch, int32_t max_pages_per_route,
                          int32_t route_list_launch, int32_t* chunk_pages, int32_t* max_chunks,
                          int32_t* units_per_wg);
+
+/*
+ * kf_partial_attn_spans -- whether a launch of `num_launch` routes of at most
+ * `max_pages_per_route` pages runs as spans on the current device, given a
+ * workspace of the queried size (or the library's scratch array):
+ * *workgroup_columns is the number of workgroups per KV head, 0 if it follows
+ * kf_partial_attn_plan instead.  A span launch cuts the pages of all its
+ * routes, one route after another, into equal parts, one per wave of one
+ * resident round of workgroups, so that routes of different lengths fill the
+ * GPU evenly; parts of a route cut by a workgroup's end leave records in the
+ * workspace, and a combine (a launch, or the merge of a fused step) reduces
+ * them.  Up to 1024 routes (827 with 16 query heads per KV head: a
+ * workgroup's share of LDS holds the table), ragged tables and equal ones
+ * whose ranges do not fill the compute units; never over a route list.
+ * Where a route is cut follows the lengths of all routes of the launch, so
+ * the last bits of its partials may change when another route grows; the
+ * same arguments give the same bits.
+ * Host only; launches nothing.  Returns as kf_partial_attn_plan, and
+ * KF_ERR_INVALID_ARG if workgroup_columns is NULL.
+ */
+int kf_partial_attn_spans(const kf_shape* shape, int32_t num_launch, int32_t max_pages_per_route,
+                          int32_t route_list_launch, int32_t* workgroup_columns);
 
 /*
  * kf_partial_attn -- local core attention of every route (Section 3.2,
@@ -264,10 +292,12 @@ int kf_merge_partials(int32_t num_seqs, int32_t num_routes, int32_t num_q_heads,
  *   kf_kv_append -> kf_partial_attn -> kf_merge_partials
  * on the same arguments (each argument as documented there; the workspace
  * is sized by kf_partial_attn_workspace_bytes), in two launches instead of
- * three (a split launch adds its combine and, over several rounds, its
- * dispatch order, as kf_partial_attn does): the workgroup that attends over
- * a tail's last page first writes the step's token into it (for fp8 pools
- * by the E4M3 append rule, re-encoding the page if needed) and attends over
+ * three (over several rounds a split launch adds its dispatch order, and split
+ * and span launches a combine unless the merge does it, which it does where
+ * nearly every sequence has one route): the workgroup, or in a span launch
+ * the wave, that attends over a tail's last page first writes the step's
+ * token into it (for fp8 pools by the E4M3 append rule, re-encoding the page
+ * if needed) and attends over
  * it, and the merge advances the tails' tok_end and raises the append's
  * flags.  All host checks of the three calls
  * are made before anything is launched.
@@ -285,7 +315,7 @@ int kf_decode_step(const kf_shape* shape, const void* q, void* k_pool, void* v_p
  * device memory or pass a workspace: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Same arguments, results,
  * flags and route updates as kf_decode_step, without workspace and
- * workspace_bytes: the chunk partials of a split launch go through a scratch
+ * workspace_bytes: the records of a split or span launch go through a scratch
  * array of KF_SCRATCH_BYTES that the library holds in each device's memory
  * from the first kernel launch on that device until the process ends.
  * Allocates nothing and calls no allocating routine.  The first call on a

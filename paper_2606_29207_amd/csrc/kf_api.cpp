@@ -399,6 +399,22 @@ int kf_partial_attn_plan(const kf_shape* shape, int32_t num_launch, int32_t max_
   return KF_OK;
 }
 
+int kf_partial_attn_spans(const kf_shape* shape, int32_t num_launch, int32_t max_pages_per_route,
+                          int32_t route_list_launch, int32_t* workgroup_columns) {
+  if (!workgroup_columns) return KF_ERR_INVALID_ARG;
+  kf::ChunkPlan plan{};
+  const int st = kf_partial_attn_plan(shape, num_launch, max_pages_per_route, route_list_launch,
+                                      &plan.chunk_pages, &plan.max_chunks, nullptr);
+  if (st != KF_OK) return st;
+  *workgroup_columns =
+      kf::plan_span(num_launch, shape->num_kv_heads, shape->num_q_heads / shape->num_kv_heads,
+                    max_pages_per_route, shape->num_page_ids,
+                    shape->kv_dtype == KF_KV_FP8_E4M3, route_list_launch == 1, plan,
+                    2 * (int64_t)kf::cu_count())
+          .wg_cols;
+  return KF_OK;
+}
+
 }  // extern "C"
 
 namespace {

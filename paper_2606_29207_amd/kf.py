@@ -38,8 +38,9 @@ KV_HEAD_MAJOR = 1
 
 # every symbol include/kf.h declares
 EXPORTS = ("kf_kv_append", "kf_partial_attn_workspace_bytes", "kf_partial_attn_plan",
-           "kf_partial_attn", "kf_partial_attn_subset", "kf_merge_partials", "kf_decode_step",
-           "kf_decode_step_no_alloc", "kf_debug_gather", "kf_status_str", "kf_version")
+           "kf_partial_attn_spans", "kf_partial_attn", "kf_partial_attn_subset",
+           "kf_merge_partials", "kf_decode_step", "kf_decode_step_no_alloc", "kf_debug_gather",
+           "kf_status_str", "kf_version")
 
 
 class KFError(RuntimeError):
@@ -79,6 +80,8 @@ def load(path: str | None = None) -> ctypes.CDLL:
     lib.kf_partial_attn_workspace_bytes.restype = sz
     lib.kf_partial_attn_plan.argtypes = [sp, i32, i32, i32, vp, vp, vp]
     lib.kf_partial_attn_plan.restype = ctypes.c_int
+    lib.kf_partial_attn_spans.argtypes = [sp, i32, i32, i32, vp]
+    lib.kf_partial_attn_spans.restype = ctypes.c_int
     lib.kf_partial_attn.argtypes = [sp, vp, vp, vp, vp, vp, vp, i32, i32, vp, vp, vp, vp, sz, vp, vp]
     lib.kf_partial_attn.restype = ctypes.c_int
     lib.kf_partial_attn_subset.argtypes = [sp, vp, vp, vp, vp, vp, vp, i32, vp, i32, i32, vp, vp, vp,
@@ -301,12 +304,24 @@ def partial_attn_workspace_bytes(shape: Shape, num_routes: int, max_pages_per_ro
 def partial_attn_plan(shape: Shape, num_launch: int, max_pages_per_route: int,
                       route_list: bool = False) -> tuple[int, int, int]:
     """kf_partial_attn_plan: (chunk_pages, max_chunks, units_per_wg) of a
-    launch of num_launch routes (route_list: a kf_partial_attn_subset launch)."""
+    launch of num_launch routes (route_list: a kf_partial_attn_subset launch)
+    that does not run as spans (partial_attn_spans)."""
     out = [ctypes.c_int32(0) for _ in range(3)]
     st = load().kf_partial_attn_plan(ctypes.byref(shape), int(num_launch), int(max_pages_per_route),
                                      1 if route_list else 0, *[ctypes.byref(o) for o in out])
     _check(st, "kf_partial_attn_plan")
     return tuple(int(o.value) for o in out)
+
+
+def partial_attn_spans(shape: Shape, num_launch: int, max_pages_per_route: int,
+                       route_list: bool = False) -> int:
+    """kf_partial_attn_spans: workgroup columns of a launch that runs as spans,
+    0 for one that follows partial_attn_plan."""
+    cols = ctypes.c_int32(0)
+    st = load().kf_partial_attn_spans(ctypes.byref(shape), int(num_launch), int(max_pages_per_route),
+                                      1 if route_list else 0, ctypes.byref(cols))
+    _check(st, "kf_partial_attn_spans")
+    return int(cols.value)
 
 
 def alloc_workspace(shape: Shape, num_routes: int, max_pages_per_route: int, device="cuda"):

@@ -18,7 +18,8 @@ hipError_t hipGetLastError(void) { return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = g_cus; return hipSuccess; }
 namespace kf {
 hipError_t launch_append(const AppendArgs&, bool, hipStream_t) { return hipSuccess; }
-hipError_t launch_partial(const PartialArgs&, bool, hipStream_t) { return hipSuccess; }
+static PartialArgs g_launch;  // the last launch
+hipError_t launch_partial(const PartialArgs& a, bool, hipStream_t) { g_launch = a; return hipSuccess; }
 hipError_t launch_merge(const MergeArgs&, hipStream_t) { return hipSuccess; }
 hipError_t launch_gather(const PartialArgs&, bool, int, int, void*, void*, hipStream_t) { return hipSuccess; }
 hipError_t scratch_address(void** out) { *out = nullptr; return hipSuccess; }
@@ -100,6 +101,19 @@ int main(int argc, char** argv) {
     const int64_t slots = 2 * (int64_t)g_cus;
     const kf::ChunkPlan c = kf::plan_chunks(R, H, maxp, kf::ragged_table(s.num_page_ids, R, maxp), fp8, list);
     const kf::SpanPlan p = kf::plan_span(R, H, G, maxp, s.num_page_ids, fp8, list, c, slots);
+    // what the query says is what the launch does, with a workspace of the queried size
+    int32_t wgs = -1;
+    CHECK(kf_partial_attn_spans(&s, R, maxp, list, &wgs) == KF_OK && wgs == p.wg_cols);
+    char* const at = reinterpret_cast<char*>((uintptr_t)1 << 30);
+    int32_t* const i32 = reinterpret_cast<int32_t*>(at);
+    float* const f32 = reinterpret_cast<float*>(at);
+    const size_t ws = kf_partial_attn_workspace_bytes(&s, R, maxp);
+    const int st =
+        list ? kf_partial_attn_subset(&s, at, at, at, f32, f32, (kf_route*)at, R, i32, R, maxp, i32,
+                                      f32, f32, at, ws, i32, nullptr)
+             : kf_partial_attn(&s, at, at, at, f32, f32, (kf_route*)at, R, maxp, i32, f32, f32, at,
+                               ws, i32, nullptr);
+    CHECK(st == KF_OK && kf::g_launch.span_cols == wgs * kf::kWaves);
     if (!p.wg_cols) continue;
     ++spans;
     // two workgroups fit the 160 KiB of a compute unit

@@ -358,6 +358,28 @@ def test_partial_attn_plan(lib):
     assert [o.value for o in out] == [-7, -7, -7]           # nothing written on error
 
 
+def test_partial_attn_spans(lib):
+    """Which launches run as spans, without a GPU (256 compute units assumed).
+    The plan of a span launch is the one that it does not take: 192 multi-head
+    sequences would stay whole, without a combine or workspace use."""
+    spans, plan = kf.partial_attn_spans, kf.partial_attn_plan
+    mha = _shape(num_seqs=192, num_q_heads=32, num_kv_heads=32, num_pages=9000, num_page_ids=8400)
+    assert plan(mha, 192, 81) == (81, 1, 2) and spans(mha, 192, 81) == 16   # 512 workgroups
+    assert spans(mha, 192, 81, route_list=True) == 0
+    llama = _shape(num_seqs=16, num_q_heads=32, num_kv_heads=8, num_pages=40000, num_page_ids=33024)
+    assert spans(llama, 64, 516) == 0                        # equal units, a full round
+    i32 = ctypes.c_int32
+    out = i32(-7)
+    call = lambda s, *a: lib.kf_partial_attn_spans(s, *a, ctypes.byref(out))  # noqa: E731
+    assert call(None, 4, 5, 0) == kf.ERR_INVALID_ARG
+    assert call(ctypes.byref(mha), -1, 5, 0) == kf.ERR_INVALID_ARG
+    assert call(ctypes.byref(mha), 4, 5, 2) == kf.ERR_INVALID_ARG
+    assert call(ctypes.byref(mha), 65536, 5, 0) == kf.ERR_UNSUPPORTED
+    assert lib.kf_partial_attn_spans(ctypes.byref(mha), 4, 5, 0, None) == kf.ERR_INVALID_ARG
+    assert out.value == -7                                   # nothing written on error
+    assert call(ctypes.byref(mha), 0, 0, 0) == 0 and out.value == 0
+
+
 def test_debug_gather_host_checks(lib):
     v = lambda x: None if x is None else ctypes.c_void_p(x)  # noqa: E731
     s = _shape()
