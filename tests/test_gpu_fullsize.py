@@ -85,7 +85,8 @@ def test_fullsize_whole_tensors(gpu, name, seed):
     st = DecodeState.from_instance(inst)
     plan = kf.partial_attn_plan(st.shape, st.routes.shape[0], st.max_pages_per_route)
     print(f"[fullsize] {name} seed {seed}: {len(inst.routes)} routes, {inst.num_pages} pages, "
-          f"plan (chunk pages, max chunks, units/workgroup) {plan}, "
+          f"plan (chunk pages, max chunks, units/workgroup) {plan}, span columns "
+          f"{kf.partial_attn_spans(st.shape, st.routes.shape[0], st.max_pages_per_route)}, "
           f"set up in {time.perf_counter() - t0:.1f}s", flush=True)
     # the oracle's state: the instance's own arrays, appended to in place
     kp, vp, ks, vs, routes = inst.k_pool, inst.v_pool, inst.k_scale, inst.v_scale, inst.routes

@@ -22,6 +22,9 @@ CASES = {
                  [2100, 1500, 33], 2),
     "hkv1": ("llama8b_32k", dict(num_seqs=4, num_q_heads=8, num_kv_heads=1, part_tokens=512),
              [900, 1, 1700, 512], 2),
+    # span launches: cut, whole and empty routes, tails in pages of their own
+    "spans_hkv8": ("llama8b_32k", dict(num_seqs=8), [9000, 17, 0, 4100, 999, 31, 16, 3500], 2),
+    "spans_fp8": ("wide_gqa_fp8", dict(num_seqs=7), [18000, 16, 0, 9001, 65, 4096, 2000], 3),
     "fp8_append": ("wide_gqa_fp8", dict(num_seqs=3, part_tokens=1024, appends=1), [3000, 2048, 1111], 3),
     "fp8_hkv2": ("wide_gqa_fp8", dict(num_seqs=4, num_q_heads=16, num_kv_heads=2, part_tokens=768, appends=1),
                  [1600, 1025, 16, 800], 2),
@@ -53,6 +56,8 @@ def test_head_major_equals_page_major(gpu, case, fused):
     _, a = _run(inst, steps, kf.KV_PAGE_MAJOR, fused)
     st, b = _run(inst, steps, kf.KV_HEAD_MAJOR, fused)
     assert st.shape.kv_layout == kf.KV_HEAD_MAJOR and st.k_pool.shape[0] == wl.num_kv_heads
+    spans = kf.partial_attn_spans(st.shape, st.routes.shape[0], st.max_pages_per_route)
+    assert (spans > 0) == case.startswith("spans"), spans
     for k in KEYS + ("k_pool", "v_pool"):
         x, y = a[k], b[k]
         if x is None:

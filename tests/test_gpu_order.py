@@ -20,32 +20,57 @@ MAX_ORDER_ITEMS = 1 << 20
 
 def _ordered(st, num_launch, route_list=False):
     """Whether a launch of num_launch routes runs in a computed order on this
-    GPU: split, with at least two work items per resident slot (two per CU)."""
+    GPU: split and not as spans, with at least two work items per resident
+    slot (two per CU)."""
     import torch
     from paper_2606_29207_amd import kf
     cp, mc, up = kf.partial_attn_plan(st.shape, num_launch, st.max_pages_per_route,
                                       route_list=route_list)
     slots = 2 * torch.cuda.get_device_properties(0).multi_processor_count
     items = mc * st.shape.num_kv_heads * num_launch
-    return mc > 1 and 2 * slots <= items <= MAX_ORDER_ITEMS, (cp, mc, up, items)
+    spans = kf.partial_attn_spans(st.shape, num_launch, st.max_pages_per_route,
+                                  route_list=route_list)
+    return (mc > 1 and spans == 0 and 2 * slots <= items <= MAX_ORDER_ITEMS,
+            (cp, mc, up, items, spans))
 
 
-def _ragged_instance(appends):
+def _ragged_instance(appends, fp8=False):
+    """More routes than a span launch takes: 20 of up to 40000 tokens, empty
+    ones among them, and 1080 of a page or two."""
     lens = [0, 37, 16, 900, 4096, 9000, 23000, 511, 3000, 12000, 7777, 40000,
             64, 2048, 15000, 1025, 6000, 300, 18000, 8191]
-    return make_instance(workload("agentic_mix", num_seqs=len(lens), part_tokens=4096,
-                                  appends=appends), seed=21, steps=4, seq_lens=lens)
+    lens += [1 + 7 * i % 31 for i in range(1080)]
+    wl = workload("agentic_mix", num_seqs=len(lens), num_q_heads=8, num_kv_heads=2,
+                  part_tokens=1 << 20, appends=appends, kv_dtype="fp8" if fp8 else "bf16")
+    return make_instance(wl, seed=21, steps=4, seq_lens=lens)
 
 
+def _small_instance():
+    """62 short sequences, a few of them longer: work for fewer than two tiles
+    per wave of a span launch, but 1488 ranges."""
+    lens = [600 if i % 7 == 3 else 90 + i for i in range(62)]
+    return make_instance(workload("agentic_mix", num_seqs=len(lens), part_tokens=8192, appends=1),
+                         seed=23, steps=3, seq_lens=lens)
+
+
+@pytest.mark.parametrize("batch", ["bf16", "fp8", "small"])
 @pytest.mark.parametrize("fused", [False, True])
-def test_ordered_split_launch_matches_oracle(gpu, fused):
+def test_ordered_split_launch_matches_oracle(gpu, fused, batch):
+    """The small batch's fused step (one route per sequence) combines its
+    records in the merge; the others' in a launch of their own."""
     from paper_2606_29207_amd.step import DecodeState
-    inst = _ragged_instance(appends=1)
+    inst = _small_instance() if batch == "small" else _ragged_instance(1, fp8=batch == "fp8")
     ok, plan = _ordered(DecodeState.from_instance(inst), len(inst.routes))
     assert ok, f"the launch should run in a computed order: plan {plan}"
-    print(f"[order] {len(inst.routes)} routes, plan (chunk pages, ranges, units/wg, items) {plan}",
+    print(f"[order] {len(inst.routes)} routes, plan (chunk pages, ranges, units/wg, items, spans) {plan}",
           flush=True)
     compare_all(host(run_gpu(inst, 3, fused=fused)), run_oracle(inst, 3))
+
+
+def _assert_ordered(inst):
+    from paper_2606_29207_amd.step import DecodeState
+    ok, plan = _ordered(DecodeState.from_instance(inst), len(inst.routes))
+    assert ok, f"the launch should run in a computed order: plan {plan}"
 
 
 def test_ordered_launch_with_bad_routes(gpu):
@@ -56,6 +81,7 @@ def test_ordered_launch_with_bad_routes(gpu):
     routes[5, 3] = routes[5, 2] + 16 * (routes[5, 5] + 1)   # more pages than page_cap
     inst.routes[:] = routes
     inst.page_ids[int(inst.routes[9, 4]) + 3] = inst.num_pages + 5   # a page outside the pool
+    _assert_ordered(inst)
     g, o = host(run_gpu(inst, 1)), run_oracle(inst, 1)
     assert g["flags"] == o["flags"] == (oracle.EFLAG_BAD_ROUTE | oracle.EFLAG_BAD_PAGE)
     compare_all(g, o)
@@ -63,6 +89,7 @@ def test_ordered_launch_with_bad_routes(gpu):
 
 def test_ordered_launch_is_bitwise_repeatable(gpu):
     inst = _ragged_instance(appends=0)
+    _assert_ordered(inst)
     runs = [host(run_gpu(inst, 1)) for _ in range(3)]
     for k in ("o_part", "lse_part", "out", "lse"):
         for r in runs[1:]:

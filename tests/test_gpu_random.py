@@ -63,8 +63,9 @@ def test_full_round_of_units_ragged_or_equal(gpu, ragged):
     """512 units (64 single-route sequences x 8 KV heads) fill whole rounds of
     the resident slots.  Equal routes stay whole, two units per workgroup;
     ragged ones (a page table well under routes x max pages; routes of
-    up to ~560 pages here, longer than the 256-page range floor) are cut
-    into page ranges.  Both match the oracle over fused steps."""
+    up to ~560 pages here, longer than the 256-page range floor) would be cut
+    into page ranges and run as spans.  Both match the oracle over fused
+    steps."""
     from paper_2606_29207_amd import kf
     from paper_2606_29207_amd.step import DecodeState
     rng = np.random.default_rng(606)
@@ -75,19 +76,23 @@ def test_full_round_of_units_ragged_or_equal(gpu, ragged):
     st = DecodeState.from_instance(inst)
     _, max_chunks, units = kf.partial_attn_plan(st.shape, st.routes.shape[0], st.max_pages_per_route)
     assert (max_chunks > 1 and units == 1) if ragged else (max_chunks == 1 and units == 2)
+    spans = kf.partial_attn_spans(st.shape, st.routes.shape[0], st.max_pages_per_route)
+    assert (spans > 0) == ragged
     del st
     o = run_oracle(inst, 2)
     compare_all(host(run_gpu(inst, 2, fused=True)), o)
 
 
 @pytest.mark.parametrize("num_seqs,tokens,plan_tail", [(56, 700, (1, 1)), (96, 700, (1, 1)),
-                                                      (120, 700, (1, 2)), (40, 1400, (3, 1))])
+                                                      (120, 700, (1, 2)), (48, 1400, (2, 1)),
+                                                      (40, 1400, (3, 1))])
 def test_equal_units_spread_over_the_cus(gpu, num_seqs, tokens, plan_tail):
     """Equal routes whose (route, KV head) units do not fill whole rounds of
     the resident slots but spread evenly over the compute units (448, 768
     and 960 units on 256 CUs) stay whole: one unit per workgroup, or two
-    where pairs leave every CU an even count (960).  320 units take the
-    fewest ranges whose work items spread evenly (3: 960 items).  They match
+    where pairs leave every CU an even count (960).  384 units take the
+    fewest ranges whose work items spread evenly (2: 768 items), and so would
+    320 (3: 960 items), which do not fill the CUs and run as spans.  They match
     the oracle over fused steps."""
     import torch
     from paper_2606_29207_amd import kf
@@ -98,6 +103,8 @@ def test_equal_units_spread_over_the_cus(gpu, num_seqs, tokens, plan_tail):
     plan = kf.partial_attn_plan(st.shape, st.routes.shape[0], st.max_pages_per_route)
     if torch.cuda.get_device_properties(0).multi_processor_count == 256:
         assert plan[1:] == plan_tail, plan
+        spans = kf.partial_attn_spans(st.shape, st.routes.shape[0], st.max_pages_per_route)
+        assert (spans > 0) == (num_seqs == 40), spans
     del st
     o = run_oracle(inst, 2)
     compare_all(host(run_gpu(inst, 2, fused=True)), o)

@@ -38,11 +38,11 @@ def _instance(case, steps, seed=5):
 
 
 def _is_span(inst):
-    """The launch rule: a ragged table with two tiles per wave."""
-    n, r, most = len(inst.page_ids), len(inst.routes), inst.max_pages_per_route
-    tile = 4 if inst.k_scale is not None else 2
-    return n * 10 < r * most * 9 and n * inst.wl.num_kv_heads >= 2 * tile * 2048 and r <= 1024 and \
-        (most > 32 or inst.wl.group <= 8)
+    from paper_2606_29207_amd import kf
+    s = kf.make_shape(inst.wl.num_seqs, inst.wl.num_q_heads, inst.wl.num_kv_heads,
+                      kf.KV_BF16 if inst.k_scale is None else kf.KV_FP8_E4M3, inst.num_pages,
+                      len(inst.page_ids), inst.scale)
+    return kf.partial_attn_spans(s, len(inst.routes), inst.max_pages_per_route) > 0
 
 
 @pytest.mark.parametrize("case", _RAGGED, ids=lambda c: f"{c[0]}q{c[1]}kv{'fp8' if c[2] else ''}")

@@ -36,6 +36,8 @@ def _assert_two_units(st, route_list=False):
     from paper_2606_29207_amd import kf
     plan = kf.partial_attn_plan(st.shape, st.routes.shape[0], st.max_pages_per_route, route_list)
     assert plan[1:] == ((1, 1) if route_list else (1, 2)), plan
+    assert kf.partial_attn_spans(st.shape, st.routes.shape[0], st.max_pages_per_route,
+                                 route_list) == 0
 
 
 def test_two_units_per_workgroup_match_oracle_and_separate_calls(gpu):

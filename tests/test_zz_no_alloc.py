@@ -2,10 +2,10 @@
 allocate: its chunk partials use the library's per-device scratch array)
 against kf_decode_step with a workspace, through the C ABI.
 
-Two calls in a row on one device, each on its own copy of the same state as
-the reference call: first a larger batch whose launch splits its units (so
-the chunk partials go through the scratch array), then a smaller one, which
-runs over what the first left in the array.  Outputs, pools, scales, route
+Calls in a row on one device, each on its own copy of the same state as
+the reference call: a batch that runs as spans, one of more routes whose ranges
+run in a computed order (their records and the order go through the scratch
+array), then a smaller one, which runs over what those left in the array.  Outputs, pools, scales, route
 rows and flags must be bit-identical to kf_decode_step's: both run the same
 kernels on the same plan."""
 import numpy as np
@@ -49,16 +49,25 @@ def _step_pair(inst):
 
 
 def test_no_alloc_step_equals_decode_step_twice(gpu):
-    big = make_instance(workload("agentic_mix", num_seqs=12, ctx_range=(1000, 40000),
-                                 part_tokens=8192), seed=3, steps=2)
+    import torch
+    from paper_2606_29207_amd import kf
+    from test_gpu_order import _ragged_instance
+    spans = make_instance(workload("agentic_mix", num_seqs=12, ctx_range=(1000, 40000),
+                                   part_tokens=8192), seed=3, steps=2)
+    ordered = _ragged_instance(appends=1)
     small = make_instance(workload("wide_gqa_fp8_decode", num_seqs=2, num_q_heads=16,
                                    num_kv_heads=2, part_tokens=1024), seed=4, steps=2,
                           seq_lens=[2500, 700])
-    import torch
-    p1 = _step_pair(big)
-    # the first launch runs in a computed dispatch order (a table in the scratch array)
+    plans = []
+    for inst, cut in ((spans, True), (ordered, False), (small, False)):
+        s = kf.make_shape(inst.wl.num_seqs, inst.wl.num_q_heads, inst.wl.num_kv_heads,
+                          kf.KV_BF16 if inst.k_scale is None else kf.KV_FP8_E4M3, inst.num_pages,
+                          len(inst.page_ids), inst.scale)
+        cols = kf.partial_attn_spans(s, len(inst.routes), inst.max_pages_per_route)
+        assert (cols > 0) == cut, cols
+        plans.append(_step_pair(inst))
+    # the second launch runs in a computed dispatch order (a table in the scratch array)
     slots = 2 * torch.cuda.get_device_properties(0).multi_processor_count
-    items = p1[1] * big.wl.num_kv_heads * len(big.routes)
-    assert 2 * slots <= items <= 1 << 20, f"plan {p1}: {items} work items"
-    p2 = _step_pair(small)
-    print(f"[no_alloc] plans {p1} then {p2}", flush=True)
+    items = plans[1][1] * ordered.wl.num_kv_heads * len(ordered.routes)
+    assert 2 * slots <= items <= 1 << 20, f"plan {plans[1]}: {items} work items"
+    print(f"[no_alloc] plans {plans}", flush=True)
