@@ -210,15 +210,19 @@ int32_t units_per_workgroup(bool fp8, bool route_list, const ChunkPlan& plan, in
 //    so they do with routes of at most 32 pages and more than 8 query heads
 //    per KV head (250 of 100-260 tokens, 16 heads: 46.5 -> 49.0 us).
 //  - Ragged tables that it leaves whole (bf16 units of at most 256 pages that
-//    fill a round, or very many) wait for their longest units only, in a launch
-//    without a combine: spans pay where the pages that the routes' reserves
-//    fall short of the longest come to 30 a slot, or 50 with more than 8 query
-//    heads per KV head, whose parts are larger.  Of 231 such tables (64-250
-//    sequences of 30-3900 tokens, 4 to 32 KV heads, groups of 1 to 16) those
-//    at the line or above gain 0-21%, but for 12 that lose 0.3-8% (65 x 8 heads of
-//    500-1500 tokens 51.3 -> 53.8 us, 96 x 12 of 65-500 37.8 -> 40.7); below
-//    it 64 x 8 heads of 500-1024 tokens lost 8%, 128 x 4 of 16 query heads
-//    17%, 96 x 8 of 400-500 29%, and some gain (65 x 8 of 1000-1500: 8%).
+//    fill a round, or very many) wait for their longest units and fullest
+//    compute units only, in a launch without a combine: spans pay where the
+//    pages that the table falls short of that come to 30 a slot, counted with
+//    as many units on every compute unit as on the fullest (unless these are
+//    under an eighth of them), or, with more than 8 query heads per KV head,
+//    whose parts are larger, to 50, counted without.
+//    Of 231 such tables (64-250 sequences of 30-3900 tokens, 4 to 32 KV heads,
+//    groups of 1 to 16) the line takes 178: they gain up to 21%, but for 11
+//    that lose 0.4-8% (65 x 8 heads of 500-1500 tokens 51.3 -> 53.8 us, 96 x 12
+//    of 65-500 37.8 -> 40.7).  Of the 53 that it leaves, 44 lost as spans (64 x
+//    8 heads of 500-1024 tokens 8%, 128 x 4 of 16 query heads 17%, 96 x 8 of
+//    400-500 29%) and 6 gained 2-8% (65 x 8 of 1000-1500; but 64 x 8 equal
+//    ones and an empty route lost 10%).
 //  - Equal tables whose chunk plan keeps units whole (they fill the GPU
 //    evenly, or are short) stay as they are: 2000 fp8 units of 44 or 125 pages
 //    lose 5-7%, 512 units 1-4%.  Split ones run as spans when units outnumber
@@ -240,7 +244,9 @@ bool span_launch(int32_t num_launch, int32_t num_kv_heads, int32_t group,
   if ((int64_t)num_page_ids * num_kv_heads < 2 * tile * slots * kWaves) return false;
   if (ragged_table(num_page_ids, num_launch, max_pages_per_route)) {
     // units < 2^26, pages < 2^31
-    const int64_t spare = units * max_pages_per_route - (int64_t)num_page_ids * num_kv_heads;
+    const int64_t cus = slots / 2, more = units % cus;
+    const int64_t held = units + (group <= 8 && more * 8 >= cus ? cus - more : 0);
+    const int64_t spare = held * max_pages_per_route - (int64_t)num_page_ids * num_kv_heads;
     if (plan.max_chunks == 1 && spare < (group <= 8 ? 30 : 50) * slots) return false;
     return max_pages_per_route > 32 || group <= 8;
   }

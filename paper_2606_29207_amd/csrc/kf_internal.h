@@ -22,7 +22,7 @@ constexpr int kMaxLaunchRoutes = 65535;  // routes per launch and KV heads: grid
 constexpr int kChunksOneWave = 8;        // ranges per unit up to which one wave combines a head
 constexpr int64_t kEarlyRecordHeads = 2048;  // most (route, head) pairs whose records load early
 constexpr int kRecordsOneWave = 8;       // mean records per (sequence, head) up to which one wave merges them
-constexpr int64_t kOneWaveGrid = 1024;   // (sequence, head) pairs above which it does
+constexpr int64_t kOneWaveGrid = 512;   // (sequence, head) pairs above which it does
 constexpr int kCombineRows = 256;        // most routes of a fused step whose merge combines records one wave a head
 constexpr int kLdsRows = 16;             // rows per sequence that a combining merge keeps in LDS
 constexpr int kLdsStride = kDim + 4;     // padded row of an output buffer in LDS

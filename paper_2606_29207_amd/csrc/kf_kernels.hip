@@ -2258,10 +2258,10 @@ hipError_t launch_merge(const MergeArgs& a, hipStream_t stream) {
   const dim3 grid(a.num_q_heads + (a.tail_route ? 1 : 0), a.num_seqs);
   const int rows = a.num_routes / a.num_seqs;  // mean rows per sequence
   // One wave per head leaves no idle waves where grids are large (64 sequences
-  // of 64 heads: step 68.3 us, with four 73.6; 217 of 8: 28.0 and 29.2); in
-  // small ones four waves cost nothing (8 of 32 heads: 23.9 and 24.0) and take
-  // a sequence of many rows faster (16 rows beside 15 sequences, 64 heads: 33.6
-  // and 40.9).
+  // of 64 heads: step 68.3 us, with four 73.6; 217 of 8: 28.0 and 29.2; 119 of
+  // 8: 13.4 and 14.1); in small ones four waves cost nothing (8 of 32 heads: 23.9
+  // and 24.0) and take a sequence of many rows faster (16 rows beside 15
+  // sequences of 64 heads, one wave 40.9, four 33.6).
   if (a.rec.ml && wide_merge(a.num_seqs, a.num_q_heads) && (rows > 0 ? rows : 1) * a.rec.places <= kRecordsOneWave)
     hipLaunchKernelGGL(HIP_KERNEL_NAME(merge_kernel<1, true>), grid, dim3(64), 0, stream, a);
   else if (a.rec.ml)
