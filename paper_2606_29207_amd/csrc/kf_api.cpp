@@ -216,13 +216,14 @@ int32_t units_per_workgroup(bool fp8, bool route_list, const ChunkPlan& plan, in
 //    as many units on every compute unit as on the fullest (unless these are
 //    under an eighth of them), or, with more than 8 query heads per KV head,
 //    whose parts are larger, to 50, counted without.
-//    Of 231 such tables (64-250 sequences of 30-3900 tokens, 4 to 32 KV heads,
-//    groups of 1 to 16) the line takes 178: they gain up to 21%, but for 11
+//    Of 201 such tables (64-250 sequences of 30-3900 tokens, 4 to 32 KV heads,
+//    groups of 1 to 16) the line takes 148: they gain up to 21%, but for 10
 //    that lose 0.4-8% (65 x 8 heads of 500-1500 tokens 51.3 -> 53.8 us, 96 x 12
 //    of 65-500 37.8 -> 40.7).  Of the 53 that it leaves, 44 lost as spans (64 x
 //    8 heads of 500-1024 tokens 8%, 128 x 4 of 16 query heads 17%, 96 x 8 of
 //    400-500 29%) and 6 gained 2-8% (65 x 8 of 1000-1500; but 64 x 8 equal
-//    ones and an empty route lost 10%).
+//    ones and an empty route lost 10%).  fp8 units, whole from 3072 on, gain
+//    2-21% in 30 of 31 such tables (237 x 16 of 129-239 tokens 77.4 -> 66.4).
 //  - Equal tables whose chunk plan keeps units whole (they fill the GPU
 //    evenly, or are short) stay as they are: 2000 fp8 units of 44 or 125 pages
 //    lose 5-7%, 512 units 1-4%.  Split ones run as spans when units outnumber
@@ -230,8 +231,8 @@ int32_t units_per_workgroup(bool fp8, bool route_list, const ChunkPlan& plan, in
 //    to -34%), or the compute units without their ranges filling these evenly:
 //    288, 400 and 416 units -1 to -25%, and bf16 320 and 352 units, whose
 //    ranges leave the last quarter of them empty, -3.6 to 0%; fp8 ones of
-//    these lose (352 units of 250 pages 74.0 -> 77.7 us), unless more than four
-//    ranges run on each.
+//    these came out even over 26 batches, at -8 to +10%, and keep their ranges
+//    unless more than four run on each.
 // Launches over a route list keep the chunk plan: the page table does not
 // describe their routes.
 namespace {
@@ -247,7 +248,7 @@ bool span_launch(int32_t num_launch, int32_t num_kv_heads, int32_t group,
     const int64_t cus = slots / 2, more = units % cus;
     const int64_t held = units + (group <= 8 && more * 8 >= cus ? cus - more : 0);
     const int64_t spare = held * max_pages_per_route - (int64_t)num_page_ids * num_kv_heads;
-    if (plan.max_chunks == 1 && spare < (group <= 8 ? 30 : 50) * slots) return false;
+    if (!fp8 && plan.max_chunks == 1 && spare < (group <= 8 ? 30 : 50) * slots) return false;
     return max_pages_per_route > 32 || group <= 8;
   }
   if (plan.max_chunks == 1) return false;

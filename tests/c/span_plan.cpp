@@ -64,6 +64,8 @@ static int rules() {
       {101, 8, 5, 65, 5584, false, true},    // 808 units: a compute unit holds four
       {101, 8, 16, 65, 5584, false, false},
       {65, 8, 4, 76, 4200, false, false},    // 520: all but eight hold two
+      {237, 16, 1, 27, 5700, true, true},    // fp8: wherever ragged
+      {237, 16, 1, 27, 5700, false, false},
       {64, 8, 4, 600, 20000, false, true},   // ragged and split
       {40, 8, 4, 500, 20000, false, true},   // 320 equal units in 3 ranges: 960 on 256 CUs
       {40, 8, 4, 500, 20000, true, false},
